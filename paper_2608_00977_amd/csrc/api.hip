@@ -246,7 +246,10 @@ struct ExtState {
     float *plan_carry = nullptr;
     int64_t plan_cap = 0;
     int32_t *err = nullptr;
-    uint32_t *unsorted = nullptr;  // the chunk's keys out of order (radix_sort)
+    // [0]: the chunk's keys out of order (radix_sort); then the lengths of
+    // the row lists of the gradient steps (ExtLists), zeroed with it
+    uint32_t *unsorted = nullptr;
+    int32_t *long_rows[kExtLists] = {};
     int next = 0;
     bool pending = false;
 };
@@ -528,6 +531,7 @@ void free_ext_buffers(tsid_ctx *c) {
     A.release(x.sort_scratch);
     A.release(x.stream);
     A.release(x.ptr);
+    for (auto &l : x.long_rows) A.release(l);
     A.release(x.plan_off);
     A.release(x.plan_nparts);
     A.release(x.plan_scan);
@@ -2270,7 +2274,7 @@ void ext_ensure(tsid_ctx *c, int64_t nnz, int32_t n_free, int32_t k) {
         }
         x.err = A.alloc<int32_t>(ERR_SLOTS);
         TSID_HIP(hipMemsetAsync(x.err, 0, ERR_SLOTS * 4, c->comp));
-        x.unsorted = A.alloc<uint32_t>(1);
+        x.unsorted = A.alloc<uint32_t>(1 + kExtLists);
     }
     if (nnz <= x.cap_nnz && n_free <= x.cap_free && k == x.k) return;
     ext_sync_all(c);  // buffers may be in use by earlier chunks
@@ -2293,6 +2297,7 @@ void ext_ensure(tsid_ctx *c, int64_t nnz, int32_t n_free, int32_t k) {
     x.sort_scratch = A.alloc<uint32_t>((int64_t)radix_scratch_elems(cn));
     x.stream = A.alloc<int2>(cn);
     x.ptr = A.alloc<int64_t>((int64_t)cf + 1);
+    for (auto &l : x.long_rows) l = A.alloc<int32_t>(cf);
     // items of at least 64 cells: at most one per row plus nnz / 64
     x.plan_cap = (int64_t)cf + cn / 64 + 1;
     x.plan_off = A.alloc<uint32_t>((int64_t)cf + 1);
@@ -2420,6 +2425,7 @@ void extend_chunk(tsid_ctx *c, int side, const int32_t *fixed_id, const int32_t 
     TSID_HIP(hipEventRecord(s.ev_staged, cs));
     // a chunk already grouped by free row (fixed ids ascending within a row,
     // as a line-by-line generator emits them) skips the sort's passes
+    fill_u32(x.unsorted, 1 + kExtLists, 0u, cs);
     keys_unsorted(x.keys, nnz, x.unsorted, cs);
     const bool alt = radix_sort(x.keys, x.vals, x.keys_alt, x.vals_alt, nnz, bits_fixed + bits_free,
                                 x.sort_scratch, cs, x.unsorted);
@@ -2495,11 +2501,13 @@ void extend_chunk(tsid_ctx *c, int side, const int32_t *fixed_id, const int32_t 
         a.degree = o->step == TSID_STEP_DEGREE;
         a.err = x.err;
         // rows long enough for the Gram form go to k_extend_gram, the others
-        // take every step in one launch of the per-cell kernel (one wave per
-        // free row in both)
+        // take every step in the per-cell kernels
         const int64_t gmin = extend_gram_min(K, o->epochs, o->clip, n_fixed);
         a.skip_from = gmin;
-        launch_extend_steps(K, a, o->epochs, cs);
+        ExtLists ext_lists;
+        for (int w = 0; w < kExtLists; ++w) ext_lists.rows[w] = x.long_rows[w];
+        ext_lists.count = x.unsorted + 1;
+        launch_extend_steps(K, a, o->epochs, nnz, ext_lists, cs);
         if (gmin > 0) {
             RidgeArgs g{};
             g.stream = x.stream;

@@ -25,6 +25,8 @@
 //    takes the update and a round-to-nearest-even bf16 copy is written beside it.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace tsid {
@@ -677,148 +679,361 @@ __global__ __launch_bounds__(kThreads) void k_block_combine(const PassArgs A, co
 }
 
 // One-sided extension steps (Section 5.2, Eq. 6 in factored form), all T of
-// them in one launch.  A free row's steps need nothing from other rows, so a
-// wave owns one free row (bucket) for the whole run: its NG lane groups split
-// the row's cells, each step they add their partial gradient sums through LDS
-// in group order, and every group applies the same update to its register
-// copy of the row (Eq. 5 with the step option and the clip).  The row starts
-// at zero and is stored once, after the last step.  The per-cell work is the
-// item pass's (process_block), so a step is the same computation as one
-// launch of the item pass on the chunk.
-// Stream records per lane per block in the extension kernel: a group's share
-// of a free row of up to G * TSID_EXT_SPL cells stays in registers.
-#ifndef TSID_EXT_SPL
-#define TSID_EXT_SPL 4
+// them in one launch.  A free row's steps need nothing from other rows, so
+// the row stays with one wave, or one workgroup of WAVES waves, for the whole
+// run, and its fixed rows are gathered once, into registers, whatever the step
+// count: the row's cells are split evenly over the lane groups (G = K / V
+// lanes, NG per wave), each group holding up to CH cells.  A step is, per
+// cell, the residual (dot product and DPP butterfly) and the gradient sum;
+// then the groups' sums are added and the row moves (Eq. 5 with the step
+// option and the clip).  The row starts at zero and is stored once.
+//
+// What bounds it: VALU issue, 2 K multiply-adds and log2 G butterfly adds per
+// cell and step; so a group only visits its share of the row's cells (the
+// share's ceiling is the same for the whole wave), cells past it are zero rows
+// with value zero (they add exactly nothing and need no masks), and the sum
+// over the groups is a reduce-scatter (WaveSum) after which each lane updates
+// only the coordinates it owns.  Measured (2 million cells, 20 steps, the
+// chunk's whole compute, before -> now; before, one wave took every row, added
+// its groups' sums through LDS and updated all coordinates in every group, and
+// a row of more than 64 cells gathered again every step):
+//   k = 128, rows of 24 cells  1,595 -> 714 us   (of 6 cells 5,568 -> 1,424)
+//   k = 128, 290 cells, 256 MB table 2,815 -> 757 us  (4 MB table 989 -> 730)
+//   k = 64, 96 cells, 2 MB table 612 -> 352 us; 384 cells 566 -> 395 us
+// Rows that take the Gram form (launch_extend_gram, fp64) keep it, also where
+// this form is now the faster one (k = 64, 96 cells, 128 MB table: 388 us here,
+// 738 us there): its sums are in fp64.
+
+// Sums over the 64 / G lane groups of a wave, and back.  sum() leaves N of
+// the V coordinates of each lane, summed over the groups, in own: halves of
+// the wave, then of each half, exchange half of their values
+// (v_permlane32_swap, v_permlane16_swap: after the swap of a and b the lower
+// part holds both copies of a and the upper part both of b, so one add sums
+// two values); inside a row of 16 lanes the exchange is by DPP, and once a
+// single value is left, the rest is an all-reduce by row rotations (each add
+// commutes, so all lanes end with the same bits).  spread() is the inverse:
+// every lane ends with all V coordinates.
+template <int G, int V>
+struct WaveSum {
+    static constexpr int N32 = V / 2;
+    static constexpr int N16 = V / 4;
+    static constexpr bool SPLIT8 = G <= 8 && N16 >= 2;
+    static constexpr int N = SPLIT8 ? N16 / 2 : N16;
+    static_assert(V % 4 == 0 && G <= 16, "four quarters of the wave, groups inside a row");
+
+    static __device__ __forceinline__ void swap32(float &a, float &b) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    }
+    static __device__ __forceinline__ void swap16(float &a, float &b) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    }
+    static __device__ __forceinline__ void sum(const float (&v)[V], float (&own)[N], bool up8) {
+        float h[N32], q[N16];
+#pragma unroll
+        for (int i = 0; i < N32; ++i) {
+            float a = v[i], b = v[i + N32];
+            swap32(a, b);
+            h[i] = a + b;
+        }
+#pragma unroll
+        for (int i = 0; i < N16; ++i) {
+            float a = h[i], b = h[i + N16];
+            swap16(a, b);
+            q[i] = a + b;
+        }
+        if constexpr (SPLIT8) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const float send = up8 ? q[i] : q[i + N], keep = up8 ? q[i + N] : q[i];
+                own[i] = keep + dpp<0x128>(send);  // row_ror:8, lane ^ 8
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                own[i] = q[i];
+                if constexpr (G <= 8) own[i] += dpp<0x128>(own[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if constexpr (G <= 4) own[i] += dpp<0x124>(own[i]);  // row_ror:4
+            if constexpr (G <= 2) own[i] += dpp<0x122>(own[i]);  // row_ror:2
+        }
+    }
+    static __device__ __forceinline__ void spread(const float (&own)[N], float (&v)[V], bool up8) {
+        float h[N32], q[N16];
+        if constexpr (SPLIT8) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const float o = dpp<0x128>(own[i]);
+                q[i] = up8 ? o : own[i];
+                q[i + N] = up8 ? own[i] : o;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) q[i] = own[i];
+        }
+#pragma unroll
+        for (int i = 0; i < N16; ++i) {
+            h[i] = q[i];
+            h[i + N16] = q[i];
+            swap16(h[i], h[i + N16]);
+        }
+#pragma unroll
+        for (int i = 0; i < N32; ++i) {
+            v[i] = h[i];
+            v[i + N32] = h[i];
+            swap32(v[i], v[i + N32]);
+        }
+    }
+};
+
+// Cells a lane group holds (CH) in the one-wave form and in the workgroup
+// forms, and how many cells a form of WAVES waves holds.  At k = 64 and 128 a
+// cell takes 8 VGPRs: 16 cells leave three waves per SIMD, 24 leave two (one
+// workgroup of 8 waves, or two of 4, per compute unit).
+#ifndef TSID_EXT_CELLS
+#define TSID_EXT_CELLS 16
+#endif
+#ifndef TSID_EXT_GROUP_CELLS
+#define TSID_EXT_GROUP_CELLS 24
+#endif
+constexpr int kExtCells = TSID_EXT_CELLS;
+constexpr int kExtGroupCells = TSID_EXT_GROUP_CELLS;
+// waves of the workgroup forms; the last one holds no cells and takes rows of
+// any length
+constexpr int kExtForms[kExtLists] = {2, 4, 8, 4};
+template <int K, int V>
+constexpr int64_t ext_capacity(int waves) { return (int64_t)waves * (64 / (K / V)) * (waves > 1 ? kExtGroupCells : kExtCells); }
+// Cells visited per branch on a group's share: two keep the dot products of
+// two cells in flight and waste at most one cell per group and step.
+#ifndef TSID_EXT_UNROLL
+#define TSID_EXT_UNROLL 2
 #endif
 
-template <int K, int V, bool BUF>
-__global__ __launch_bounds__(kThreads) void k_extend_steps(const PassArgs A, int32_t steps) {
+// All steps of one free row by WAVES waves (WAVES = 1: this wave alone).
+// red: LDS of 2 x WAVES x 64 x N floats (WAVES > 1).
+template <int K, int V, bool BUF, int WAVES, bool STREAM>
+__device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row, const int64_t rb, const int64_t deg,
+                                           const int32_t steps, float *red) {
     constexpr int G = K / V;
     constexpr int NG = 64 / G;
-    constexpr int SPL = (G * TSID_EXT_SPL) % chunk_cells<G>() == 0 ? TSID_EXT_SPL : chunk_cells<G>() / G;
-    constexpr int SB = G * SPL;
+    constexpr int CH = WAVES > 1 ? kExtGroupCells : kExtCells;
+    constexpr int UN = TSID_EXT_UNROLL;
+    static_assert(CH % UN == 0, "whole branches");
+    constexpr int SPLR = (CH + G - 1) / G;
+    using W = WaveSum<G, V>;
     const int lane = threadIdx.x & 63;
-    const int grp = lane / G, lg = lane % G, wv = threadIdx.x >> 6;
-    const int64_t row = (int64_t)blockIdx.x * kWaves + wv;
-    if (row >= A.rows) return;  // whole waves leave together
-    const int64_t rb = A.ptr[row], deg = A.ptr[row + 1] - rb;
-    if (A.skip_from > 0 && deg >= A.skip_from) return;  // the Gram-form kernel's row
-    const int64_t beg = rb + grp * deg / NG, end = rb + (grp + 1) * deg / NG;
+    const int wv = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
+    const int grp = wv * NG + lane / G, lg = lane % G;
+    const bool up8 = (lane & 8) != 0;
+    constexpr int64_t groups = (int64_t)WAVES * NG;
+    const int64_t beg = rb + grp * deg / groups, end = rb + (grp + 1) * deg / groups;
     const int64_t last = end - 1;
     const float s = A.degree ? 1.0f / (float)(deg > 1 ? deg : 1) : 1.0f;
     const YTable Yt = make_ytable<BUF>(A, K * 4);
-    __shared__ float red[kWaves][NG][K];
-    float x[V];
+    float x[V], xo[W::N];
 #pragma unroll
     for (int v = 0; v < V; ++v) x[v] = 0.f;
-    const uint32_t xp[V / 2] = {};  // bf16 pairs: unused in fp32
-    bool bad = false;
-    // A group whose share of the row fits one stream block keeps its records
-    // in registers for all steps (extension rows are short); longer shares
-    // stream their records again each step.
-    const bool one_block = end - beg <= SB;
-    int2 keep[SPL], bufA[SPL], bufB[SPL];
-    if (end > beg) {
 #pragma unroll
-        for (int c = 0; c < SPL; ++c) {
-            const int64_t jj = beg + c * G + lg;
-            keep[c] = load_cell(A.stream + (jj < last ? jj : last));
-        }
-    }
-    // The row's gradient sum (the groups' partial sums in group order) and
-    // the update of every group's copy of the row.
-    auto update = [&](const float (&acc)[V]) {
-        store_f32<V>(&red[wv][grp][lg * V], acc);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        float tot[V];
-        load_f32<V>(&red[wv][0][lg * V], tot);
-        for (int g = 1; g < NG; ++g) {
-            float part[V];
-            load_f32<V>(&red[wv][g][lg * V], part);
+    for (int i = 0; i < W::N; ++i) xo[i] = 0.f;
+    // The gradient sum over the groups (and the waves, in wave order), the
+    // update of the coordinates this lane owns, and the row back to all lanes.
+    auto update = [&](const float (&acc)[V], const int st) {
+        float own[W::N];
+        W::sum(acc, own, up8);
+        if constexpr (WAVES > 1) {
+            // one barrier per step: the two halves of red alternate
+            float *buf = red + (st & 1) * (WAVES * 64 * W::N);
 #pragma unroll
-            for (int v = 0; v < V; ++v) tot[v] += part[v];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();  // every lane has read red before the next step writes it
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int i = 0; i < W::N; ++i) buf[(wv * W::N + i) * 64 + lane] = own[i];
+            __syncthreads();
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const float g = 2.0f * A.lam * x[v] - 2.0f * tot[v];
-            const float d = clipped_step(g, s, A.clip, A.xi);
-            x[v] = x[v] + A.lr * d;
-            bad |= !__builtin_isfinite(x[v]);
+            for (int i = 0; i < W::N; ++i) {
+                own[i] = buf[i * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < WAVES; ++w) own[i] += buf[(w * W::N + i) * 64 + lane];
+            }
         }
+#pragma unroll
+        for (int i = 0; i < W::N; ++i) {
+            const float g = 2.0f * A.lam * xo[i] - 2.0f * own[i];
+            xo[i] += A.lr * clipped_step(g, s, A.clip, A.xi);
+        }
+        W::spread(xo, x, up8);
     };
-    constexpr int CH = chunk_cells<G>();
-    static_assert(CH <= SB && CH % G == 0, "a chunk lies inside the first stream block");
-    if (deg <= (int64_t)NG * CH) {
-        // Every group's share fits one chunk (shares differ by at most one
-        // cell; the test is on the row, so the whole wave takes this branch):
-        // the fixed rows are gathered once, into registers, and every step
-        // reuses them, with the per-cell code's arithmetic in its order.
-        float yc[CH][V], rc[CH];
-        const int64_t left = end - beg;
-        if (end > beg) {
+    if constexpr (!STREAM) {
+        // the largest share of a group, the same for every lane
+        const int most = __builtin_amdgcn_readfirstlane((int)((deg + groups - 1) / groups));
+        const int left = (int)(end - beg);
+        int2 rec[SPLR];
 #pragma unroll
-            for (int t = 0; t < CH; ++t) {
-                const int b = group_bcast<G>(keep[t / G].x, t % G);
-                rc[t] = __int_as_float(group_bcast<G>(keep[t / G].y, t % G));
+        for (int c = 0; c < SPLR; ++c) rec[c] = make_int2(0, 0);
+        if (left > 0) {
+#pragma unroll
+            for (int c = 0; c < SPLR; ++c) {
+                const int64_t jj = beg + c * G + lg;
+                rec[c] = load_cell(A.stream + (jj < last ? jj : last));
+            }
+        }
+        float yc[CH][V], rc[CH];
+#pragma unroll
+        for (int t0 = 0; t0 < CH; t0 += UN) {
+            if (t0 < most) {
+#pragma unroll
+            for (int t = t0; t < t0 + UN; ++t) {
+                const int b = group_bcast<G>(rec[t / G].x, t % G);
+                rc[t] = __int_as_float(group_bcast<G>(rec[t / G].y, t % G));
 #pragma unroll
                 for (int c = 0; c < V / 4; ++c) {
-                    const uint4 q = ygather16<BUF>(Yt, b, K * 4, Lanes<G, V, false>::coord(lg, c) * 4);
+                    uint4 q = make_uint4(0u, 0u, 0u, 0u);
+                    if (left > 0) q = ygather16<BUF>(Yt, b, K * 4, Lanes<G, V, false>::coord(lg, c) * 4);
                     yc[t][4 * c + 0] = __uint_as_float(q.x);
                     yc[t][4 * c + 1] = __uint_as_float(q.y);
                     yc[t][4 * c + 2] = __uint_as_float(q.z);
                     yc[t][4 * c + 3] = __uint_as_float(q.w);
                 }
             }
+            }
+        }
+#pragma unroll
+        for (int t0 = 0; t0 < CH; t0 += UN) {
+            if (t0 < most) {
+#pragma unroll
+            for (int t = t0; t < t0 + UN; ++t) {
+                const bool in = t < left;
+                if (!in) rc[t] = 0.f;
+#pragma unroll
+                for (int v = 0; v < V; ++v) yc[t][v] = in ? yc[t][v] : 0.f;
+            }
+            }
         }
         for (int st = 0; st < steps; ++st) {
             float acc[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] = 0.f;
-            if (end > beg) {
 #pragma unroll
-                for (int t = 0; t < CH; ++t) {
-                    float d = 0.f;
+            for (int t0 = 0; t0 < CH; t0 += UN) {
+                if (t0 < most) {
 #pragma unroll
-                    for (int v = 0; v < V; ++v) d += x[v] * yc[t][v];
-                    d = group_sum<G>(d);
-                    const float e = t < left ? rc[t] - d : 0.f;
+                for (int t = t0; t < t0 + UN; ++t) {
+                    float d0 = 0.f, d1 = 0.f;
+#pragma unroll
+                    for (int v = 0; v < V; v += 2) {
+                        d0 += x[v] * yc[t][v];
+                        d1 += x[v + 1] * yc[t][v + 1];
+                    }
+                    const float e = rc[t] - group_sum<G>(d0 + d1);
 #pragma unroll
                     for (int v = 0; v < V; ++v) acc[v] += e * yc[t][v];
                 }
+                }
             }
-            update(acc);
+            update(acc, st);
         }
     } else {
+        // longer than a compute unit's registers hold: the groups walk their
+        // shares through the item pass's blocks again every step
+        constexpr int SPL = 4 * G % chunk_cells<G>() == 0 ? 4 : chunk_cells<G>() / G;
+        constexpr int SB = G * SPL;
+        const uint32_t xp[V / 2] = {};  // bf16 pairs: unused in fp32
+        int2 bufA[SPL], bufB[SPL];
         for (int st = 0; st < steps; ++st) {
             float acc[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] = 0.f;
             float e2 = 0.f;
-            if (one_block) {
-                if (end > beg)
-                    process_block<K, V, false, false, BUF, false, SPL>(A, Yt, beg, end, last, lg, keep, bufB, x,
-                                                                       xp, acc, e2);
-            } else {
+            if (end > beg) {
 #pragma unroll
-                for (int c = 0; c < SPL; ++c) bufA[c] = keep[c];
-                for (int64_t j0 = beg; j0 < end; j0 += SB) {
-                    process_block<K, V, false, false, BUF, true, SPL>(A, Yt, j0, end, last, lg, bufA, bufB, x, xp,
-                                                                      acc, e2);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int c = 0; c < SPL; ++c) bufA[c] = bufB[c];
+                for (int c = 0; c < SPL; ++c) {
+                    const int64_t jj = beg + c * G + lg;
+                    bufA[c] = load_cell(A.stream + (jj < last ? jj : last));
                 }
             }
-            update(acc);
+            for (int64_t j0 = beg; j0 < end; j0 += SB) {
+                process_block<K, V, false, false, BUF, true, SPL>(A, Yt, j0, end, last, lg, bufA, bufB, x, xp, acc,
+                                                                  e2);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int c = 0; c < SPL; ++c) bufA[c] = bufB[c];
+            }
+            update(acc, st);
         }
     }
     if (grp == 0) store_coords<G, V, false>(A.Xn + row * K, lg, x);
+    // a value that left the finite range never comes back (the update adds to
+    // it), so the last one tells
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < W::N; ++i) bad |= !__builtin_isfinite(xo[i]);
     if (bad) A.err[ERR_NONFINITE] = 1;
+}
+
+// The rows longer than one wave's capacity, listed by the workgroup form that
+// takes them (the lists' order is of no account: rows are independent).  One
+// thread per row and one atomic add per list and workgroup: adds to one
+// address from every row's wave took 15 ns each.
+template <int K, int V>
+__global__ __launch_bounds__(kThreads) void k_extend_lists(const PassArgs A, const ExtLists L) {
+    __shared__ uint32_t n[kExtLists], base[kExtLists];
+    if (threadIdx.x < kExtLists) n[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t row = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    int w = -1;
+    uint32_t at = 0;
+    if (row < A.rows) {
+        const int64_t deg = A.ptr[row + 1] - A.ptr[row];
+        if (deg > ext_capacity<K, V>(1) && !(A.skip_from > 0 && deg >= A.skip_from)) {
+            w = 0;
+            while (w < kExtLists - 1 && deg > ext_capacity<K, V>(kExtForms[w])) ++w;
+            at = atomicAdd(&n[w], 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kExtLists && n[threadIdx.x]) base[threadIdx.x] = atomicAdd(L.count + threadIdx.x, n[threadIdx.x]);
+    __syncthreads();
+    if (w >= 0) L.rows[w][base[w] + at] = (int32_t)row;
+}
+
+// One wave per free row of at most one wave's capacity; longer ones are the
+// workgroup forms'.
+template <int K, int V, bool BUF>
+__global__ __launch_bounds__(kThreads, K >= 64 ? 3 : 4) void k_extend_steps(const PassArgs A, int32_t steps) {
+    const int64_t row =
+        (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (row >= A.rows) return;  // whole waves leave together
+    const int64_t rb = A.ptr[row], deg = A.ptr[row + 1] - rb;
+    if (deg > ext_capacity<K, V>(1)) return;
+    if (A.skip_from > 0 && deg >= A.skip_from) return;  // the Gram-form kernel's row
+    extend_row<K, V, BUF, 1, false>(A, row, rb, deg, steps, nullptr);
+}
+
+// The listed rows, one workgroup of WAVES waves each, dealt in turn (the lists
+// come in about row order, so neighbours in length); the next row's place is
+// read while this one's steps run.
+template <int K, int V, bool BUF, int WAVES, bool STREAM>
+__global__ __launch_bounds__(64 * WAVES) void k_extend_group(const PassArgs A, int32_t steps, const int32_t *list,
+                                                             const uint32_t *count) {
+    __shared__ float red[2 * WAVES * 64 * WaveSum<K / V, V>::N];
+    const uint32_t n = *count;
+    uint32_t q = blockIdx.x;
+    if (q >= n) return;
+    int64_t row = list[q], rb = A.ptr[row], re = A.ptr[row + 1];
+    for (;;) {
+        q += gridDim.x;
+        const int64_t nrow = q < n ? list[q] : row;
+        const int64_t nrb = A.ptr[nrow], nre = A.ptr[nrow + 1];
+        __syncthreads();  // the previous row's last reads of red are done
+        extend_row<K, V, BUF, WAVES, STREAM>(A, row, rb, re - rb, steps, red);
+        if (q >= n) return;  // the same for the whole workgroup
+        row = nrow;
+        rb = nrb;
+        re = nre;
+    }
 }
 
 template <int K>
@@ -957,20 +1172,35 @@ void item_pass_pair_kv(const PassArgs &a0, const PassArgs &a1, hipStream_t s, hi
     TSID_HIP(hipGetLastError());
 }
 
-template <int K, int V, bool BF16>
-void extend_steps_kv(const PassArgs &a, int32_t steps, hipStream_t s) {
-    if constexpr (BF16) {
-        fail(TSID_E_INVAL, "the extension runs in fp32");
-    } else {
-        const int grid = ceil_div(a.rows, (int64_t)kWaves);
-        if (grid <= 0) return;  // steps == 0 still runs: it stores the zero start
-        const bool buf = a.y_rows * (int64_t)K * 4 < (int64_t(1) << 31);
-        if (buf)
-            hipLaunchKernelGGL((k_extend_steps<K, V, true>), dim3(grid), dim3(kThreads), 0, s, a, steps);
-        else
-            hipLaunchKernelGGL((k_extend_steps<K, V, false>), dim3(grid), dim3(kThreads), 0, s, a, steps);
+template <int K, int V, bool BUF>
+void extend_steps_buf(const PassArgs &a, int32_t steps, int64_t nnz, const ExtLists &l, hipStream_t s) {
+    hipLaunchKernelGGL((k_extend_steps<K, V, BUF>), dim3(ceil_div(a.rows, (int64_t)kWaves)), dim3(kThreads), 0, s, a,
+                       steps);
+    TSID_HIP(hipGetLastError());
+    if (nnz <= ext_capacity<K, V>(1)) return;
+    hipLaunchKernelGGL((k_extend_lists<K, V>), dim3(ceil_div(a.rows, (int64_t)kThreads)), dim3(kThreads), 0, s, a, l);
+    TSID_HIP(hipGetLastError());
+    // at most nnz / (capacity + 1) rows are longer than a form's capacity
+    auto group = [&](auto kernel, int w, int waves) {
+        const int64_t most = std::min<int64_t>(a.rows, nnz / (ext_capacity<K, V>(w ? kExtForms[w - 1] : 1) + 1));
+        if (most <= 0) return;
+        // twice as many workgroups as fit at two waves per SIMD
+        const int64_t grid = std::min<int64_t>(most, 2 * 256 * 8 / waves);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), 0, s, a, steps, (const int32_t *)l.rows[w],
+                           (const uint32_t *)(l.count + w));
         TSID_HIP(hipGetLastError());
-    }
+    };
+    group(k_extend_group<K, V, BUF, kExtForms[0], false>, 0, kExtForms[0]);
+    group(k_extend_group<K, V, BUF, kExtForms[1], false>, 1, kExtForms[1]);
+    group(k_extend_group<K, V, BUF, kExtForms[2], false>, 2, kExtForms[2]);
+    group(k_extend_group<K, V, BUF, kExtForms[3], true>, 3, kExtForms[3]);
+}
+
+template <int K, int V>
+void extend_steps_k(const PassArgs &a, int32_t steps, int64_t nnz, const ExtLists &l, hipStream_t s) {
+    if (a.rows <= 0) return;  // steps == 0 still runs: it stores the zero start
+    if (a.y_rows * (int64_t)K * 4 < (int64_t(1) << 31)) extend_steps_buf<K, V, true>(a, steps, nnz, l, s);
+    else extend_steps_buf<K, V, false>(a, steps, nnz, l, s);
 }
 
 template <int K, int V, bool BF16>
@@ -1063,9 +1293,23 @@ void launch_item_pass_sched(int K, int prec, const PassArgs &a, const int32_t *s
     TSID_DISPATCH_K(K, item_pass_sched_kv, a, sched, n_wg, s, ev0, ev1)
 }
 
-void launch_extend_steps(int K, const PassArgs &a, int32_t steps, hipStream_t s) {
-    const int prec = TSID_FP32;
-    TSID_DISPATCH_K(K, extend_steps_kv, a, steps, s)
+// V = 4 and 8 coordinates per lane: at k = 64, groups of 8 lanes add a dot
+// product in three butterfly steps for 8 cells at once (16 lanes and 4 steps
+// for 4 cells cost a third more instructions per cell).
+template <int K>
+constexpr int kExtV = K >= 64 ? 8 : 4;
+#define TSID_EXT_DISPATCH(K_, FN, ...)                       \
+    switch (K_) {                                            \
+        case 8: FN<8, kExtV<8>>(__VA_ARGS__); break;         \
+        case 16: FN<16, kExtV<16>>(__VA_ARGS__); break;      \
+        case 32: FN<32, kExtV<32>>(__VA_ARGS__); break;      \
+        case 64: FN<64, kExtV<64>>(__VA_ARGS__); break;      \
+        case 128: FN<128, kExtV<128>>(__VA_ARGS__); break;   \
+        default: fail(TSID_E_INVAL, "unsupported rank");     \
+    }
+
+void launch_extend_steps(int K, const PassArgs &a, int32_t steps, int64_t nnz, const ExtLists &l, hipStream_t s) {
+    TSID_EXT_DISPATCH(K, extend_steps_k, a, steps, nnz, l, s)
 }
 
 namespace {

@@ -67,7 +67,7 @@ void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, uin
 size_t radix_scratch_elems(int64_t n);
 bool radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, int64_t n,
                 int nbits, uint32_t *scratch, hipStream_t s, const uint32_t *unsorted = nullptr);
-// *unsorted = 1 if some key is smaller than the one before it, else 0.
+// *unsorted = 1 if some key is smaller than the one before it (else left as it is).
 void keys_unsorted(const uint64_t *keys, int64_t n, uint32_t *unsorted, hipStream_t s);
 
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
@@ -204,10 +204,16 @@ void launch_block_bounds(const int2 *stream, const int64_t *ptr, int32_t rows, i
 // give the degrees).
 void launch_block_combine(int K, int prec, const PassArgs &a, const float *part, int32_t n_blocks, hipStream_t s,
                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// `steps` one-sided extension steps from zero in one launch, one wave per
-// bucket (a.rows buckets over a.stream / a.ptr; fp32; a.X unused, the result
-// goes to a.Xn; a non-finite update stores 1 in a.err[ERR_NONFINITE]).
-void launch_extend_steps(int K, const PassArgs &a, int32_t steps, hipStream_t s);
+// `steps` one-sided extension steps from zero (a.rows buckets over a.stream /
+// a.ptr, nnz cells; fp32; a.X unused, the result goes to a.Xn; a non-finite
+// update stores 1 in a.err[ERR_NONFINITE]): one wave per short bucket, then one
+// workgroup per longer bucket, from the lists that the first launch leaves.
+constexpr int kExtLists = 4;
+struct ExtLists {
+    int32_t *rows[kExtLists];  // each a.rows long: the buckets of each workgroup form
+    uint32_t *count;           // the lists' lengths, zero before the launch
+};
+void launch_extend_steps(int K, const PassArgs &a, int32_t steps, int64_t nnz, const ExtLists &l, hipStream_t s);
 // Items one wave holds for rank K and precision prec (the item pass's groups
 // per wave): buckets whose items stay inside one such run need no fixup.
 int items_per_wave(int K, int prec);

@@ -397,7 +397,6 @@ bool radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *va
 }
 
 void keys_unsorted(const uint64_t *keys, int64_t n, uint32_t *unsorted, hipStream_t s) {
-    fill_u32(unsorted, 1, 0u, s);
     if (n <= 1) return;
     k_keys_unsorted<<<grid_for(n, 256), 256, 0, s>>>(keys, n, unsorted);
     TSID_HIP(hipGetLastError());

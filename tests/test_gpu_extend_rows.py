@@ -1,0 +1,70 @@
+"""The per-cell extension steps (Section 5.2; k_extend_steps and
+k_extend_group) at the edges of what one wave and each workgroup form hold:
+rows of no cells, one cell, and one below, at and one above every capacity,
+against the oracle's one-sided steps of the same cells (1e-4 relative per row,
+the fp32 bar of the extension: 20 steps of sums of a few thousand terms, a
+few 1e-7 each).  The Gram form is off, so every row takes the per-cell form.
+A second run in chunks gives the same bits: a row's form depends on its own
+length alone."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import note
+from test_gpu_extend_gram import _chunk, _gram_env, _row_err, _run, _set_rank
+
+pytestmark = pytest.mark.gpu
+
+# cells that one wave holds, and workgroups of 2, 4 and 8 waves: lane groups of
+# k / 4 (k < 64) or k / 8 lanes, 16 cells each in the one-wave form, 24 in the others
+GROUPS = {8: 32, 16: 16, 32: 8, 64: 8, 128: 4}
+CAPS = {k: [16 * g, 48 * g, 96 * g, 192 * g] for k, g in GROUPS.items()}
+
+
+@pytest.fixture(scope="module")
+def T():
+    import paper_2608_00977_amd as tsid
+    t = tsid.Tsid(0)
+    yield t
+    t.close()
+
+
+@pytest.mark.parametrize("k", [8, 16, 32, 64, 128])
+@pytest.mark.parametrize("step,clip", [("degree", "printed"), ("sum", True)])
+def test_rows_at_capacity_edges_match_oracle(T, k, step, clip):
+    from paper_2608_00977_amd import make_opts
+    caps = CAPS[k]
+    lengths = [0, 1, 2, GROUPS[k] - 1, GROUPS[k] + 1]
+    lengths += [c + d for c in caps for d in (-1, 0, 1)] + [0, caps[3] + 77, 2 * caps[1] + 3]
+    n_fixed = caps[3] + 500
+    F, fixed, free, r = _chunk(7 + k, k, n_fixed, lengths)
+    _set_rank(T, k)
+    lr = 0.05 if step == "degree" else 0.2 / max(lengths)
+    opts = make_opts(epochs=20, lam=0.05, lr=lr, step=step, clip=clip, xi=0.05)
+    note(f"extend rows k={k} {step} clip={clip} capacities={caps}")
+    with _gram_env(-1):
+        X = _run(T, F, fixed, free, r, len(lengths), opts)
+        st, Xo = oracle.extend(fixed, free, r, len(lengths), F, 20, 0.05, lr, step, clip, 0.05)
+        assert st == 0
+        err = _row_err(X, Xo)
+        assert err.max() <= 1e-4, (err.max(), lengths[int(err.argmax())])
+        assert np.all(X[np.asarray(lengths) == 0] == 0.0)
+        half = len(lengths) // 2
+        parts = []
+        for lo, hi in ((0, half), (half, len(lengths))):
+            sel = (free >= lo) & (free < hi)
+            parts.append(_run(T, F, fixed[sel], free[sel] - lo, r[sel], hi - lo, opts))
+        np.testing.assert_array_equal(X, np.concatenate(parts))
+
+
+def test_nonfinite_step_is_reported_from_every_form(T):
+    """A step size that overflows: E_NONFINITE at sync whichever form the row takes."""
+    import paper_2608_00977_amd as tsid
+    k = 32
+    _set_rank(T, k)
+    for n in [3] + [c for c in CAPS[k]] + [CAPS[k][3] + 1]:
+        F, fixed, free, r = _chunk(n, k, n + 10, [n])
+        note(f"extend rows non-finite n={n}")
+        with _gram_env(-1), pytest.raises(tsid.TsidError) as e:
+            _run(T, F, fixed, free, r, 1, tsid.make_opts(epochs=30, lam=0.0, lr=1e30, step="sum"))
+        assert e.value.status == 7
