@@ -15,16 +15,18 @@
 //     A[l%16][l/16] and the B operand B[l/16][l%16] of v_mfma_f64_16x16x4f64,
 //     so block (I, J) of the Gram matrix accumulates with one MFMA per block
 //     pair I <= J (10 at k = 64).  Lane l, slot j of a result holds
-//     C[4 j + l/16][l%16].  The right-hand side accumulates per lane and is
-//     summed over the four cell slots at the end.
-//  2. The blocks go through LDS (and their mirror images), lane i reads row i
-//     and adds lambda on the diagonal.
-//  3. Cholesky G = L L^T, right-looking, with row i of the trailing matrix in
-//     lane i's registers: per column j, lane j's diagonal and every lane's
-//     L[i][j] are broadcast with readlane, and each lane updates its row.
-//     Entries above the diagonal are updated too and never read.
-//  4. L z = b column by column in registers, then L^T x = z column by column
-//     with the rows of L read back from LDS.
+//     C[4 j + l/16][l%16].  The right-hand side accumulates per lane, over the
+//     cells of its quarter of the wave.
+//  2. Cholesky G = U^T U on the matrix cores, four rows at a time, the blocks
+//     never leaving the accumulators.  Slot s of block row I holds rows
+//     16 I + 4 s + l/16, and that is both the A operand of its transpose and
+//     a B operand.  Per group of four rows: the 4 x 4 diagonal block (broadcast
+//     with readlane) is factored and inverted by every lane, M = L^-1; one
+//     product M x slot per block column gives the rows of U; and the trailing
+//     blocks (J, L) take -U_J^T U_L, one product each.
+//  3. U^T z = b goes along (z = M b of the group, the rest of b less its rows
+//     of U times z, per quarter), then U x = z, group by group from the last:
+//     a row's product with x by a sum over its 16 lanes, then M^T.
 // A pivot that is not positive (lambda = 0 and fewer independent cells than
 // k) raises the non-finite error; a row without cells gets x = 0.
 #include <hip/hip_ext.h>
@@ -56,49 +58,65 @@ struct RidgeShape {
 };
 
 // Gram blocks (block pairs I <= J) and right-hand side of one free row's
-// cells b0 .. b1 (b1 > b0), by one wave with the operand layout above.  Four
-// groups of four cells are loaded before their products, so each lane keeps
-// four gathers per block in flight; loads past the row's end re-read its
-// last cell and are masked.
+// cells b0 .. b1 (b1 > b0), by one wave with the operand layout above.  A ring
+// of U groups of four cells: a group's fixed rows load while the U - 1 groups
+// before it take their products (640 cycles a group at k = 64, 192 at k = 32),
+// and its records load a round earlier, so a row alone on its SIMD (long
+// rows are few) does not wait for the two memory round trips, and a group's
+// conversions issue under the products of the one before.  Loads past the
+// row's end re-read its last cell and count as zero.
 template <int K>
 __device__ __forceinline__ void gram_line(const RidgeArgs &A, int64_t b0, int64_t b1, int lane,
                                           d4 (&acc)[RidgeShape<K>::NP], double (&rhs)[RidgeShape<K>::NB]) {
     using S = RidgeShape<K>;
-    constexpr int U = 4;
+    constexpr int U = K >= 64 ? 4 : 8;
     const int lr = lane & 15, lq = lane >> 4;
 #pragma unroll
     for (int q = 0; q < S::NP; ++q) acc[q] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int I = 0; I < S::NB; ++I) rhs[I] = 0.0;
-    for (int64_t c0 = b0; c0 < b1; c0 += 4 * U) {
-        int2 rec[U];
+    // the round's first cell and how many are left from it (as far as a round
+    // and the loads ahead of it reach)
+    const int2 *first = A.stream + b0;
+    auto left_from = [&](int64_t c0) { return (int)(b1 - c0 < (1 << 16) ? b1 - c0 : (1 << 16)); };
+    int left = left_from(b0);
+    int2 rec[U];
+    float raw[U][S::NB], val[U];
+    auto load_record = [&](int u, int ahead) {
+        const int c = ahead + 4 * u + lq;
+        rec[u] = first[c < left ? c : left - 1];
+    };
+    auto load_row = [&](int u) {
+        val[u] = __int_as_float(rec[u].y);
+        const float *p = A.F + (int64_t)rec[u].x * K;
+#pragma unroll
+        for (int I = 0; I < S::NB; ++I) raw[u][I] = p[(K % 16 == 0 || 16 * I + lr < K) ? 16 * I + lr : K - 1];
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_record(u, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_row(u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_record(u, 4 * U);
+    for (int64_t c0 = b0; c0 < b1; c0 += 4 * U, first += 4 * U) {
+        left = left_from(c0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t c = c0 + 4 * u + lq;
-            rec[u] = A.stream[c < b1 ? c : b1 - 1];
-        }
-        double pv[U][S::NB], rv[U];
+            const bool in = 4 * u + lq < left;
+            const double rv = in ? (double)val[u] : 0.0;
+            double pv[S::NB];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = c0 + 4 * u + lq < b1;
-            rv[u] = in ? (double)__int_as_float(rec[u].y) : 0.0;
-            const float *p = A.F + (int64_t)rec[u].x * K;
-#pragma unroll
-            for (int I = 0; I < S::NB; ++I) {
-                const int col = (K % 16 == 0 || 16 * I + lr < K) ? 16 * I + lr : K - 1;
-                const float v = p[col];
-                pv[u][I] = (in && (K % 16 == 0 || 16 * I + lr < K)) ? (double)v : 0.0;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
+            for (int I = 0; I < S::NB; ++I)
+                pv[I] = (in && (K % 16 == 0 || 16 * I + lr < K)) ? (double)raw[u][I] : 0.0;
+            load_row(u);
+            load_record(u, 8 * U);
             int q = 0;
 #pragma unroll
             for (int I = 0; I < S::NB; ++I) {
-                rhs[I] = fma(rv[u], pv[u][I], rhs[I]);
+                rhs[I] = fma(rv, pv[I], rhs[I]);
 #pragma unroll
                 for (int J = I; J < S::NB; ++J, ++q)
-                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[u][I], pv[u][J], acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[I], pv[J], acc[q], 0, 0, 0);
             }
         }
     }
@@ -138,69 +156,165 @@ __device__ __forceinline__ double gram_to_lds(const d4 (&acc)[RidgeShape<K>::NP]
     return b;
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Sum over the four lanes l % 16 + {0, 16, 32, 48}, in every one of them.
+__device__ __forceinline__ double sum_quarters(double v) {
+    uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    v = __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+        __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    u = __builtin_bit_cast(uint64_t, v);
+    const auto lo2 = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi2 = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi2[0] << 32) | lo2[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi2[1] << 32) | lo2[1]);
+}
+
+// 1 / sqrt(d) for a pivot d (a pivot that is not positive marks the row bad
+// and counts as 1): the hardware's estimate and two third-order Newton steps
+// r <- r (1 + e/2 + 3 e^2 / 8), e = 1 - d r^2.
+__device__ __forceinline__ double pivot_rsqrt(double d, bool &bad) {
+    bad |= !(d > 0.0);
+    d = d > 0.0 ? d : 1.0;
+    double r = __builtin_amdgcn_rsq(d);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = fma(-d * r, r, 1.0);
+        r = fma(r * e, fma(0.375, e, 0.5), r);
+    }
+    return r;
+}
+
+// One free row per wave, four to a workgroup; no LDS.  What bounds it: at
+// k = 64 the fp64 matrix cores (64 cycles a product, 10 per four cells and 120
+// for the factorisation) and the chain through the 16 groups of four rows.
+// k = 64, rows of about 97 cells: 446 -> 199 us a chunk of 10,000 rows (the
+// earlier form kept a row of the trailing matrix per lane and broadcast each
+// column element by element with readlane: 64 dependent steps, half of the
+// lanes idle).
 template <int K>
-__global__ __launch_bounds__(64) void k_ridge_rows(const RidgeArgs A) {
+__global__ __launch_bounds__(256, 2) void k_ridge_rows(const RidgeArgs A) {
     using S = RidgeShape<K>;
-    __shared__ double G[K * S::PITCH];
-    const int lane = threadIdx.x;
-    const int64_t f = blockIdx.x;  // free row
-    if (f >= A.rows) return;
+    constexpr int NB = S::NB;
+    const int lane = threadIdx.x & 63;
+    const int64_t f = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // free row
+    if (f >= A.rows) return;  // whole waves leave together
     const int64_t b0 = A.ptr[f], b1 = A.ptr[f + 1];
     if (b0 == b1) {  // no cells: the minimiser is 0
         if (lane < K) A.X[f * K + lane] = 0.f;
         return;
     }
-    // 1.-2. Gram blocks and right-hand side, the blocks through LDS
+    const int lr = lane & 15, lq = lane >> 4;
     d4 acc[S::NP];
-    double rhs[S::NB];
+    double rhs[NB];  // this quarter's share of b[16 I + lr]
     gram_line<K>(A, b0, b1, lane, acc, rhs);
-    double b = gram_to_lds<K>(acc, rhs, G, lane);
-    __syncthreads();
-    const int ri = lane < K ? lane : K - 1;  // lanes past k mirror the last row (never read back)
-    double g[K];
+    auto at = [](int I, int J) { return I * NB - I * (I - 1) / 2 + J - I; };  // block (I, J), I <= J
+    // lambda on the diagonal (coordinates past k: 1, they stay apart)
 #pragma unroll
-    for (int c = 0; c < K; ++c) g[c] = G[ri * S::PITCH + c] + ((c == lane) ? (double)A.lambda : 0.0);
-    // 3. Cholesky, right-looking; lane i ends with L[i][0..i] in g[0..i]
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (lr == 4 * j + lq) acc[at(I, I)][j] += 16 * I + lr < K ? (double)A.lambda : 1.0;
+    const int ma = lr & 3;  // the row of M in this lane's A operand; its column is lq
+    double mv[NB][4], zv[NB][4];  // per group: M[ma][lq], and z of row 4 s + lq
     bool bad = false;
-    double dinv = 1.0;  // 1 / L[i][i] of this lane's row
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        const double djj = readlane_f64(g[j], j);
-        bad |= !(djj > 0.0);
-        const double ljj = sqrt(djj > 0.0 ? djj : 1.0);
-        const double inv = 1.0 / ljj;
-        const double lij = (lane == j) ? ljj : g[j] * inv;
-        dinv = (lane == j) ? inv : dinv;
-        g[j] = (lane >= j) ? lij : g[j];
+    for (int I = 0; I < NB; ++I) {
 #pragma unroll
-        for (int l = j + 1; l < K; ++l) g[l] = fma(-lij, readlane_f64(lij, l), g[l]);
+        for (int s = 0; s < 4; ++s) {
+            const double g = acc[at(I, I)][s];
+            auto el = [&](int a, int c) { return readlane_f64(g, 16 * a + 4 * s + c); };
+            const double d00 = el(0, 0), d01 = el(0, 1), d02 = el(0, 2), d03 = el(0, 3);
+            const double d11 = el(1, 1), d12 = el(1, 2), d13 = el(1, 3), d22 = el(2, 2), d23 = el(2, 3), d33 = el(3, 3);
+            const double i0 = pivot_rsqrt(d00, bad);
+            const double l10 = d01 * i0, l20 = d02 * i0, l30 = d03 * i0;
+            const double i1 = pivot_rsqrt(fma(-l10, l10, d11), bad);
+            const double l21 = fma(-l10, l20, d12) * i1, l31 = fma(-l10, l30, d13) * i1;
+            const double i2 = pivot_rsqrt(fma(-l21, l21, fma(-l20, l20, d22)), bad);
+            const double l32 = fma(-l21, l31, fma(-l20, l30, d23)) * i2;
+            const double i3 = pivot_rsqrt(fma(-l32, l32, fma(-l31, l31, fma(-l30, l30, d33))), bad);
+            const double m10 = -(l10 * i0) * i1, m21 = -(l21 * i1) * i2, m32 = -(l32 * i2) * i3;
+            const double m20 = -fma(l21, m10, l20 * i0) * i2, m31 = -fma(l32, m21, l31 * i1) * i3;
+            const double m30 = -fma(l32, m20, fma(l31, m10, l30 * i0)) * i3;
+            // M[ma][lq], zero above the diagonal
+            const double c0 = ma == 0 ? i0 : ma == 1 ? m10 : ma == 2 ? m20 : m30;
+            const double c1 = ma == 1 ? i1 : ma == 2 ? m21 : ma == 3 ? m31 : 0.0;
+            const double c2 = ma == 2 ? i2 : ma == 3 ? m32 : 0.0;
+            const double c3 = ma == 3 ? i3 : 0.0;
+            const double m = lq == 0 ? c0 : lq == 1 ? c1 : lq == 2 ? c2 : c3;
+            mv[I][s] = m;
+            // the group's rows of U: every slot of the product holds them
+            double u[NB];
+#pragma unroll
+            for (int J = I; J < NB; ++J) {
+                const d4 p = __builtin_amdgcn_mfma_f64_16x16x4f64(m, acc[at(I, J)][s], d4{0.0, 0.0, 0.0, 0.0}, 0, 0, 0);
+                u[J] = p[s];
+                acc[at(I, J)][s] = u[J];
+            }
+#pragma unroll
+            for (int J = I; J < NB; ++J) {
+                if (J == I && s == 3) continue;  // block row I is done
+                // A rows of this block row that are already U are zero: they stay as they are
+                const double n = J > I || lr >= 4 * (s + 1) ? -u[J] : 0.0;
+#pragma unroll
+                for (int L = J; L < NB; ++L)
+                    acc[at(J, L)] = __builtin_amdgcn_mfma_f64_16x16x4f64(n, u[L], acc[at(J, L)], 0, 0, 0);
+            }
+            // z = M b for the group, and its part taken out of the rest of b
+            const double bs = sum_quarters(rhs[I]);
+            const double y0 = readlane_f64(bs, 4 * s), y1 = readlane_f64(bs, 4 * s + 1),
+                         y2 = readlane_f64(bs, 4 * s + 2), y3 = readlane_f64(bs, 4 * s + 3);
+            const double z0 = i0 * y0, z1 = fma(m10, y0, i1 * y1), z2 = fma(m20, y0, fma(m21, y1, i2 * y2)),
+                         z3 = fma(m30, y0, fma(m31, y1, fma(m32, y2, i3 * y3)));
+            const double z = lq == 0 ? z0 : lq == 1 ? z1 : lq == 2 ? z2 : z3;
+            zv[I][s] = z;
+#pragma unroll
+            for (int J = I; J < NB; ++J) rhs[J] = fma(-u[J], z, rhs[J]);
+        }
     }
-    // 4a. L z = b (column-oriented): lane c finishes z_c, the lanes below take it out
+    // U x = z: x[16 I + lr] in every quarter, zero until its group is solved
+    double x[NB];
 #pragma unroll
-    for (int c = 0; c < K; ++c) {
-        const double zc = readlane_f64(b * dinv, c);
-        b = (lane == c) ? zc : ((lane > c) ? fma(-g[c], zc, b) : b);
+    for (int I = 0; I < NB; ++I) x[I] = 0.0;
+#pragma unroll
+    for (int I = NB - 1; I >= 0; --I) {
+#pragma unroll
+        for (int s = 3; s >= 0; --s) {
+            double t = 0.0;
+#pragma unroll
+            for (int J = I; J < NB; ++J) t = fma(acc[at(I, J)][s], x[J], t);
+            t += dpp_f64<0xB1>(t);
+            t += dpp_f64<0x4E>(t);
+            t += dpp_f64<0x141>(t);
+            t += dpp_f64<0x140>(t);
+            const double w = zv[I][s] - t;  // row 4 s + lq
+            const double w0 = readlane_f64(w, 0), w1 = readlane_f64(w, 16), w2 = readlane_f64(w, 32),
+                         w3 = readlane_f64(w, 48);
+            // x of row lq: sum over a of M[a][lq] w_a, the four lanes of a quad
+            double v = mv[I][s] * (ma == 0 ? w0 : ma == 1 ? w1 : ma == 2 ? w2 : w3);
+            v += dpp_f64<0xB1>(v);
+            v += dpp_f64<0x4E>(v);
+            const double x0 = readlane_f64(v, 0), x1 = readlane_f64(v, 16), x2 = readlane_f64(v, 32),
+                         x3 = readlane_f64(v, 48);
+            const double xs = ma == 0 ? x0 : ma == 1 ? x1 : ma == 2 ? x2 : x3;
+            x[I] = (lr >> 2) == s ? xs : x[I];
+        }
     }
-    // 4b. L^T x = z: rows of L back through LDS (lane i reads L[r][i])
-    __syncthreads();
+    double xl = x[0];  // coordinate `lane`
+#pragma unroll
+    for (int I = 1; I < NB; ++I) xl = lq == I ? x[I] : xl;
     if (lane < K) {
-#pragma unroll
-        for (int c = 0; c < K; ++c)
-            if (c <= lane) G[lane * S::PITCH + c] = g[c];
-    }
-    __syncthreads();
-    double x = 0.0;
-#pragma unroll
-    for (int r = K - 1; r >= 0; --r) {
-        const double xr = readlane_f64(b * dinv, r);
-        x = (lane == r) ? xr : x;
-        if (lane < r) b = fma(-G[r * S::PITCH + lane], xr, b);
-    }
-    bad = __builtin_amdgcn_ballot_w64(bad) != 0;  // a bad pivot anywhere spoils the whole row
-    if (lane < K) {
-        const float xf = (float)x;
+        const float xf = (float)xl;
         A.X[f * K + lane] = xf;
-        if (bad || !__builtin_isfinite(xf)) A.err[ERR_NONFINITE] = 1;
+        if (bad || !__builtin_isfinite(xf)) A.err[ERR_NONFINITE] = 1;  // a bad pivot spoils the whole row
     }
 }
 
@@ -264,7 +378,7 @@ __global__ __launch_bounds__(64) void k_extend_gram(const RidgeArgs A) {
 
 template <int K>
 void ridge_k(const RidgeArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_ridge_rows<K>, dim3((unsigned)a.rows), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_ridge_rows<K>, dim3((unsigned)ceil_div(a.rows, 4)), dim3(256), 0, s, a);
     TSID_HIP(hipGetLastError());
 }
 
