@@ -58,17 +58,25 @@ size_t scan_scratch_elems(int64_t n);
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, uint32_t *scratch,
               hipStream_t s);
 
-// Stable LSD radix sort of (key, value) pairs on the low `nbits` bits of the
-// key, 8 bits per pass.  Ping-pongs between the two buffers; returns true if
-// the sorted result ends in the *_alt buffers.  scratch: radix_scratch_elems(n).
-// unsorted (device, or null): a flag from keys_unsorted; when it holds 0 the
-// input is already in key order and the passes only leave it in the buffer
+// Whether the keys of a sort are out of order, as a kernel before it found
+// them: *word == mark if so (marks differ from sort to sort, so the word needs
+// no clearing).  No word: not known.
+struct SortFlag {
+    uint32_t *word = nullptr;
+    uint32_t mark = 0;
+};
+
+// Stable LSD radix sort of (key, value) pairs on bits bit0 .. bit0 + nbits - 1
+// of the key (nbits <= 64), 8 bits per pass.  Ping-pongs between the two
+// buffers; returns true if the sorted result ends in the *_alt buffers.
+// scratch: radix_scratch_elems(n), whose first radix_ctl_elems() words are
+// cleared here unless ctl_zeroed says that they are.  unsorted: when its word
+// says that the input is in key order the passes only leave it in the buffer
 // the return value names.
 size_t radix_scratch_elems(int64_t n);
-bool radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, int64_t n,
-                int nbits, uint32_t *scratch, hipStream_t s, const uint32_t *unsorted = nullptr);
-// *unsorted = 1 if some key is smaller than the one before it (else left as it is).
-void keys_unsorted(const uint64_t *keys, int64_t n, uint32_t *unsorted, hipStream_t s);
+int radix_ctl_elems();
+bool radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, int64_t n, int bit0,
+                int nbits, uint32_t *scratch, hipStream_t s, SortFlag unsorted = {}, bool ctl_zeroed = false);
 
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 void fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
@@ -102,10 +110,12 @@ void ptr_from_keys(const uint64_t *keys, int64_t n, int32_t rows, int low_bits, 
 // (hi << lo_bits | lo) -> (lo << hi_bits | hi).
 void swap_key_halves(const uint64_t *keys, int64_t n, int lo_bits, int hi_bits, uint64_t *out,
                      hipStream_t s);
-// Extension chunk keys: key = free << bits_fixed | fixed; out-of-range ids -> ERR_RANGE.
+// Extension chunk keys: key = free << bits_fixed | fixed; out-of-range ids ->
+// ERR_RANGE; the order flag; and zeros in the n_zero words at `zero` (nothing
+// happens for an empty chunk).
 void chunk_keys(const int32_t *fixed_id, const int32_t *free_id, const float *r, int64_t nnz,
                 int64_t n_fixed, int32_t n_free, int bits_fixed, uint64_t *keys, uint32_t *vals,
-                int32_t *err, hipStream_t s);
+                int32_t *err, SortFlag unsorted, uint32_t *zero, int n_zero, hipStream_t s);
 
 // Work plan of a bucketed stream: every bucket (row) becomes
 // max(1, ceil(deg / E)) items of at most E entries.  item_off has rows + 1

@@ -6,6 +6,8 @@
 // Everything here is deterministic: counts may use LDS atomics, but every
 // output position comes from prefix sums over a fixed element order, so the
 // buckets are bit-identical from run to run.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace tsid {
@@ -93,45 +95,98 @@ __global__ void k_scatter_map(const int32_t *ids, int32_t count, int32_t *map) {
 }
 
 // ---------------------------------------------------------------- radix sort
+//
+// Stable LSD sort, 8 bits a pass, one launch for the digit counts of all
+// passes and one per pass: a tile's place among the tiles before it comes from
+// their published counts (chained scan with look-back), so no pass reads its
+// keys twice or waits for separate scan launches, and a sort whose input turns
+// out to be in order costs passes + 1 empty launches.  What bounds a pass: 24 B
+// of memory traffic per element, and the writes, which go through LDS so that
+// a tile's elements of one digit leave together.  Per pass of 7.2 M elements: 65
+// us with counts, three scan launches and direct writes, now 41 (a share of
+// the counts among them); a chunk in line order pays 27 us of empty launches
+// instead of 84.
 
-// Input already in key order: *unsorted stays 0 and the passes do nothing
-// (see radix_sort).
-__global__ void k_keys_unsorted(const uint64_t *keys, int64_t n, uint32_t *unsorted) {
-    bool bad = false;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x + 1; j < n;
-         j += (int64_t)gridDim.x * blockDim.x)
-        bad |= keys[j - 1] > keys[j];
-    if (bad) *unsorted = 1u;
-}
+constexpr uint32_t kMaxPasses = 8;
+// words at the start of the scratch: the tile tickets and the digit counts of each pass
+constexpr int kSortCtl = kMaxPasses * 257;
 
-__global__ __launch_bounds__(kThreads) void k_radix_hist(const uint64_t *keys, int64_t n, int shift,
-                                                         uint32_t *counts, int nb, const uint32_t *unsorted) {
-    if (unsorted && *unsorted == 0u) return;
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
+// The digit counts of every pass, and zeros in the first pass's tile states.
+template <typename State>
+__global__ __launch_bounds__(kThreads) void k_radix_hist(const uint64_t *keys, int64_t n, int bit0, int passes,
+                                                         uint32_t *ctl, State *state, int64_t state_n,
+                                                         SortFlag unsorted) {
+    if (unsorted.word && *unsorted.word != unsorted.mark) return;
+    __shared__ uint32_t h[kMaxPasses][256];
+    const int t = threadIdx.x, lane = t & 63;
+    for (int p = 0; p < passes; ++p) h[p][t] = 0;
+    const int64_t step = (int64_t)gridDim.x * kThreads;
+    const int64_t id = (int64_t)blockIdx.x * kThreads + t;
+    for (int64_t j = id; j < state_n; j += step) state[j] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int it = 0; it < kSortItems; ++it) {
-        int64_t j = base + (int64_t)it * kThreads + threadIdx.x;
-        if (j < n) atomicAdd(&h[(uint32_t)(keys[j] >> shift) & 255u], 1u);
+    // whole waves go round together, so that a digit which the wave shares
+    // (the high digits of nearly sorted keys) counts with one add
+    for (int64_t j0 = id - lane; j0 < n; j0 += step) {
+        const bool in = j0 + lane < n;
+        const uint64_t key = (in ? keys[j0 + lane] : keys[n - 1]) >> bit0;
+        const uint64_t live = __ballot(in);
+        for (int p = 0; p < passes; ++p) {
+            const uint32_t d = (uint32_t)(key >> (8 * p)) & 255u;
+            const uint32_t d0 = __builtin_amdgcn_readfirstlane((int)d);
+            if (__ballot(in && d != d0) == 0) {
+                if (lane == 0) atomicAdd(&h[p][d0], (uint32_t)__popcll(live));
+            } else if (in) {
+                atomicAdd(&h[p][d], 1u);
+            }
+        }
     }
     __syncthreads();
-    counts[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+    for (int p = 0; p < passes; ++p)
+        if (h[p][t]) atomicAdd(&ctl[kMaxPasses + p * 256 + t], h[p][t]);
 }
 
-// Stable scatter: elements are ranked in index order (round, wave, lane).
-// With unsorted pointing at 0 (input in key order) the pass only copies its
+// Inclusive sum over the 256 threads of a block (lds: 4 words).
+__device__ __forceinline__ uint32_t block_sum_incl(uint32_t v, uint32_t *lds) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(v, off, 64);
+        if (lane >= off) v += o;
+    }
+    if (lane == 63) lds[w] = v;
+    __syncthreads();
+    for (int x = 0; x < w; ++x) v += lds[x];
+    __syncthreads();
+    return v;
+}
+
+// One pass.  A tile of 4,096 elements, taken in ticket order, so that every
+// tile before this one has started: it ranks its elements by digit (wave w
+// holds elements w * 1024 .. + 1023 in order; lanes with equal digits rank by
+// lane), publishes its count of each digit, then thread d walks back over the
+// tiles before it, adding their counts of digit d, until it meets one whose
+// total up to there is known, and publishes its own total.  A tile publishes
+// its counts before it waits, and waits only for tiles with smaller tickets,
+// so every wait ends.  State word: 2 high bits (0 nothing, 1 the tile's count,
+// 2 the total of all tiles up to it), the rest the number; words carry flag
+// and number together, so no fence is needed.  `next` is the other pass's
+// states, zeroed here for it.
+// With the flag saying that the input was in order, the pass only copies its
 // tile when copy_if_sorted is set (the last of an odd number of passes, whose
 // result the caller expects in the other buffer).
-__global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint64_t *kin, const uint32_t *vin,
-                                                            uint64_t *kout, uint32_t *vout,
-                                                            int64_t n, int shift,
-                                                            const uint32_t *offs, int nb,
-                                                            const uint32_t *unsorted, int copy_if_sorted) {
-    __shared__ uint32_t s_base[256];
-    __shared__ uint32_t s_cnt[4][256];
+template <typename State>
+__global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint64_t *kin, const uint32_t *vin, uint64_t *kout,
+                                                            uint32_t *vout, int64_t n, int shift, int pass,
+                                                            uint32_t *ctl, State *state, State *next,
+                                                            SortFlag unsorted, int copy_if_sorted) {
+    constexpr int kBits = sizeof(State) * 8;
+    constexpr State kNum = (State(1) << (kBits - 2)) - 1, kCount = State(1) << (kBits - 2),
+                    kTotal = State(2) << (kBits - 2);
+    __shared__ uint64_t s_key[kSortTile];
+    __shared__ uint32_t s_val[kSortTile];
+    __shared__ uint32_t s_cnt[4][256], s_off[256], s_pos[256], s_sum[4], s_tile;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (unsorted && *unsorted == 0u) {
+    if (unsorted.word && *unsorted.word != unsorted.mark) {
         if (copy_if_sorted) {
             for (int it = 0; it < kSortItems; ++it) {
                 const int64_t j = (int64_t)blockIdx.x * kSortTile + (int64_t)it * kThreads + t;
@@ -143,39 +198,99 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint64_t *kin,
         }
         return;
     }
-    s_base[t] = offs[(int64_t)t * nb + blockIdx.x];
+    if (t == 0) s_tile = atomicAdd(&ctl[pass], 1u);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) s_cnt[x][t] = 0;
+    __syncthreads();
+    const int64_t tile = s_tile, base = tile * kSortTile;
+    const int m = (int)(n - base < kSortTile ? n - base : kSortTile);  // elements of the tile
+    const uint32_t before_digit = block_sum_incl(ctl[kMaxPasses + pass * 256 + t], s_sum) -
+                                  ctl[kMaxPasses + pass * 256 + t];  // elements of smaller digits
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int it = 0; it < kSortItems; ++it) {
-        s_cnt[0][t] = 0;
-        s_cnt[1][t] = 0;
-        s_cnt[2][t] = 0;
-        s_cnt[3][t] = 0;
-        __syncthreads();
-        const int64_t j = base + (int64_t)it * kThreads + t;
-        const bool valid = j < n;
-        const uint64_t key = valid ? kin[j] : 0ull;
-        const uint32_t val = valid ? vin[j] : 0u;
-        const uint32_t d = (uint32_t)(key >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
+    uint64_t key[kSortItems];
+    uint32_t val[kSortItems], rank[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const int e = w * (kSortTile / 4) + i * 64 + lane;
+        key[i] = e < m ? kin[base + e] : ~0ull;
+        val[i] = e < m ? vin[base + e] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const bool in = w * (kSortTile / 4) + i * 64 + lane < m;
+        const uint32_t d = (uint32_t)(key[i] >> shift) & 255u;
+        uint64_t peers = __ballot(in);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const bool bit = (d >> b) & 1u;
             const uint64_t bb = __ballot(bit);
             peers &= bit ? bb : ~bb;
         }
-        const uint32_t rank = (uint32_t)__popcll(peers & lt);
-        if (valid && rank == 0) s_cnt[w][d] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = s_base[d] + rank;
-            for (int ww = 0; ww < w; ++ww) pos += s_cnt[ww][d];
-            kout[pos] = key;
-            vout[pos] = val;
+        const uint32_t first = (uint32_t)__popcll(peers & lt);
+        const uint32_t had = s_cnt[w][d];
+        rank[i] = had + first;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (in && first == 0) s_cnt[w][d] = had + (uint32_t)__popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // thread t: digit t
+    uint32_t total = 0;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const uint32_t c = s_cnt[x][t];
+        s_cnt[x][t] = total;
+        total += c;
+    }
+    State *row = state + tile * 256;
+    __hip_atomic_store(row + t, (tile == 0 ? kTotal : kCount) | (State)total, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    next[tile * 256 + t] = 0;
+    const uint32_t local = block_sum_incl(total, s_sum) - total;
+    s_off[t] = local;
+    // eight tiles' words in flight: one at a time, the tiles of a first round
+    // of workgroups would wait for half as many load latencies as there are tiles
+    State excl = 0;
+    auto word = [&](int64_t q) {
+        return q >= 0 ? __hip_atomic_load(state + q * 256 + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kTotal;
+    };
+    bool found = tile == 0;
+    for (int64_t q = tile - 1; !found; q -= 8) {
+        State v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = word(q - x);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            if (found) continue;
+            while ((v[x] >> (kBits - 2)) == 0) {
+                __builtin_amdgcn_s_sleep(1);
+                v[x] = word(q - x);
+            }
+            excl += v[x] & kNum;
+            found = (v[x] >> (kBits - 2)) == 2;
         }
-        __syncthreads();
-        s_base[t] += s_cnt[0][t] + s_cnt[1][t] + s_cnt[2][t] + s_cnt[3][t];
-        __syncthreads();
+    }
+    if (tile > 0)
+        __hip_atomic_store(row + t, kTotal | (State)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_pos[t] = before_digit + (uint32_t)excl - local;  // where the tile's element at place 0 would go
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        if (w * (kSortTile / 4) + i * 64 + lane < m) {
+            const uint32_t d = (uint32_t)(key[i] >> shift) & 255u;
+            const uint32_t at = s_off[d] + s_cnt[w][d] + rank[i];
+            s_key[at] = key[i];
+            s_val[at] = val[i];
+        }
+    }
+    __syncthreads();
+    for (int j = t; j < m; j += kThreads) {
+        const uint64_t k = s_key[j];
+        const uint32_t to = s_pos[(uint32_t)(k >> shift) & 255u] + (uint32_t)j;
+        kout[to] = k;
+        vout[to] = s_val[j];
     }
 }
 
@@ -295,20 +410,29 @@ __global__ void k_swap_key_halves(const uint64_t *keys, int64_t n, int lo_bits, 
     }
 }
 
-__global__ void k_chunk_keys(const int32_t *fixed_id, const int32_t *free_id, const float *r,
-                             int64_t nnz, int64_t n_fixed, int32_t n_free, int bits_fixed,
-                             uint64_t *keys, uint32_t *vals, int32_t *err) {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nnz;
-         j += (int64_t)gridDim.x * blockDim.x) {
-        int32_t fx = fixed_id[j], fr = free_id[j];
-        if (fx < 0 || fx >= n_fixed || fr < 0 || fr >= n_free) {
-            err[ERR_RANGE] = 1;
-            fx = 0;
-            fr = 0;
-        }
-        keys[j] = ((uint64_t)(uint32_t)fr << bits_fixed) | (uint32_t)fx;
+// Keys and values of an extension chunk; *unsorted.word = unsorted.mark if some
+// key is smaller than the one before it; `zero` (n_zero words) is cleared for
+// the kernels that follow.
+__global__ void k_chunk_keys(const int32_t *fixed_id, const int32_t *free_id, const float *r, int64_t nnz,
+                             int64_t n_fixed, int32_t n_free, int bits_fixed, uint64_t *keys, uint32_t *vals,
+                             int32_t *err, SortFlag unsorted, uint32_t *zero, int n_zero) {
+    if (blockIdx.x == 0)
+        for (int x = threadIdx.x; x < n_zero; x += blockDim.x) zero[x] = 0u;
+    bool range = false, order = false;
+    auto key_of = [&](int64_t j) {
+        const int32_t fx = fixed_id[j], fr = free_id[j];
+        const bool ok = fx >= 0 && fx < n_fixed && fr >= 0 && fr < n_free;
+        range |= !ok;
+        return ok ? ((uint64_t)(uint32_t)fr << bits_fixed) | (uint32_t)fx : 0ull;
+    };
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t k = key_of(j);
+        keys[j] = k;
         vals[j] = __float_as_uint(r[j]);
+        order |= j > 0 && key_of(j - 1) > k;
     }
+    if (range) err[ERR_RANGE] = 1;
+    if (order) *unsorted.word = unsorted.mark;
 }
 
 __global__ void k_plan_count(const int64_t *ptr, int32_t rows, int32_t E, uint32_t *nparts) {
@@ -364,42 +488,47 @@ void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, uin
     TSID_HIP(hipGetLastError());
 }
 
+// The counts of a tile's state words fit 30 bits below 2^30 elements.
+static int state_words(int64_t n) { return n < (int64_t(1) << 30) ? 1 : 2; }
+
 size_t radix_scratch_elems(int64_t n) {
-    const int64_t nb = (n + kSortTile - 1) / kSortTile;
-    const int64_t counts = 256 * (nb > 0 ? nb : 1);
-    return (size_t)counts + scan_scratch_elems(counts);
+    const int64_t nb = n > 0 ? (n + kSortTile - 1) / kSortTile : 1;
+    return (size_t)(kSortCtl + 2 * nb * 256 * state_words(n));
 }
 
-bool radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, int64_t n,
-                int nbits, uint32_t *scratch, hipStream_t s, const uint32_t *unsorted) {
-    if (n <= 1) return false;
+int radix_ctl_elems() { return kSortCtl; }
+
+template <typename State>
+static bool radix_passes(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, int64_t n, int bit0,
+                         int passes, uint32_t *scratch, hipStream_t s, SortFlag unsorted) {
     const int nb = ceil_div(n, kSortTile);
-    const int64_t nc = 256 * (int64_t)nb;
-    uint32_t *counts = scratch, *scan_tmp = scratch + nc;
-    const int passes = (nbits + 7) / 8;
+    const int64_t ns = (int64_t)nb * 256;
+    State *state = reinterpret_cast<State *>(scratch + kSortCtl);
+    k_radix_hist<State><<<std::min(nb, 512), kThreads, 0, s>>>(keys, n, bit0, passes, scratch, state, ns, unsorted);
+    TSID_HIP(hipGetLastError());
     bool alt = false;
     for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
         const uint64_t *kin = alt ? keys_alt : keys;
         const uint32_t *vin = alt ? vals_alt : vals;
         uint64_t *kout = alt ? keys : keys_alt;
         uint32_t *vout = alt ? vals : vals_alt;
-        k_radix_hist<<<nb, kThreads, 0, s>>>(kin, n, shift, counts, nb, unsorted);
-        TSID_HIP(hipGetLastError());
-        scan_u32(counts, counts, nc, nullptr, scan_tmp, s);  // (its values unused when the passes skip)
-        const int copy_if_sorted = (p == passes - 1) && (passes & 1);
-        k_radix_scatter<<<nb, kThreads, 0, s>>>(kin, vin, kout, vout, n, shift, counts, nb, unsorted,
-                                                copy_if_sorted);
+        k_radix_scatter<State><<<nb, kThreads, 0, s>>>(kin, vin, kout, vout, n, bit0 + 8 * p, p, scratch,
+                                                       state + (p & 1) * ns, state + ((p + 1) & 1) * ns, unsorted,
+                                                       (p == passes - 1) && (passes & 1));
         TSID_HIP(hipGetLastError());
         alt = !alt;
     }
     return alt;
 }
 
-void keys_unsorted(const uint64_t *keys, int64_t n, uint32_t *unsorted, hipStream_t s) {
-    if (n <= 1) return;
-    k_keys_unsorted<<<grid_for(n, 256), 256, 0, s>>>(keys, n, unsorted);
-    TSID_HIP(hipGetLastError());
+bool radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, int64_t n, int bit0,
+                int nbits, uint32_t *scratch, hipStream_t s, SortFlag unsorted, bool ctl_zeroed) {
+    if (n <= 1) return false;
+    if (!ctl_zeroed) fill_u32(scratch, kSortCtl, 0u, s);
+    const int passes = (nbits + 7) / 8;
+    return state_words(n) == 1
+               ? radix_passes<uint32_t>(keys, vals, keys_alt, vals_alt, n, bit0, passes, scratch, s, unsorted)
+               : radix_passes<uint64_t>(keys, vals, keys_alt, vals_alt, n, bit0, passes, scratch, s, unsorted);
 }
 
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s) {
@@ -476,12 +605,12 @@ void swap_key_halves(const uint64_t *keys, int64_t n, int lo_bits, int hi_bits, 
     TSID_HIP(hipGetLastError());
 }
 
-void chunk_keys(const int32_t *fixed_id, const int32_t *free_id, const float *r, int64_t nnz,
-                int64_t n_fixed, int32_t n_free, int bits_fixed, uint64_t *keys, uint32_t *vals,
-                int32_t *err, hipStream_t s) {
+void chunk_keys(const int32_t *fixed_id, const int32_t *free_id, const float *r, int64_t nnz, int64_t n_fixed,
+                int32_t n_free, int bits_fixed, uint64_t *keys, uint32_t *vals, int32_t *err, SortFlag unsorted,
+                uint32_t *zero, int n_zero, hipStream_t s) {
     if (nnz <= 0) return;
-    k_chunk_keys<<<grid_for(nnz, 256), 256, 0, s>>>(fixed_id, free_id, r, nnz, n_fixed, n_free,
-                                                    bits_fixed, keys, vals, err);
+    k_chunk_keys<<<grid_for(nnz, 256), 256, 0, s>>>(fixed_id, free_id, r, nnz, n_fixed, n_free, bits_fixed, keys,
+                                                    vals, err, unsorted, zero, n_zero);
     TSID_HIP(hipGetLastError());
 }
 
