@@ -2441,13 +2441,9 @@ void extend_chunk(tsid_ctx *c, int side, const int32_t *fixed_id, const int32_t 
     TSID_HIP(hipStreamWaitEvent(cs, s.ev_flushed, 0));
     if (adam) {
         adam_ensure(c, s, n_free, adam->n_b, K);
-        const int64_t nc = (int64_t)n_free * adam->n_b, nq = (int64_t)n_free * adam_slices(adam->n_b) * K;
-        if (nc) {
-            TSID_HIP(hipMemsetAsync(s.Cst, 0, (size_t)nc * 4, cs));
-            TSID_HIP(hipMemsetAsync(s.Mst, 0, (size_t)nc * 4, cs));
-            TSID_HIP(hipMemsetAsync(s.Vst, 0, (size_t)nc * 4, cs));
-            TSID_HIP(hipMemsetAsync(s.qpart, 0, (size_t)nq * 4, cs));
-        }
+        const int64_t nc = (int64_t)n_free * adam->n_b;
+        // the first step starts from zero coefficients and moments by itself
+        if (nc && adam->o->steps == 0) fill_f32(s.Cst, nc, 0.f, cs);
         AdamArgs a{};
         a.stream = x.stream;
         a.ptr = x.ptr;
@@ -2478,6 +2474,7 @@ void extend_chunk(tsid_ctx *c, int side, const int32_t *fixed_id, const int32_t 
         a.n_items_ub = (int64_t)n_free + nnz / E + 1;
         a.E = E;
         a.carry = x.plan_carry;
+        a.items_per_wave = items_per_wave(K, TSID_FP32);
         a.n_fixed = n_fixed;
         launch_adam(K, a, adam->o->steps, cs);
     } else if (ridge) {

@@ -455,9 +455,10 @@ __device__ __forceinline__ void process_block(const PassArgs &A, const YTable &Y
 #define TSID_OCCUPANCY
 #endif
 
-// Workgroup `bid` of one side's item pass.
-template <int K, int V, bool BF16, bool LOSS_ONLY, bool BUF, bool PE>
-__device__ __forceinline__ void item_pass_group(const PassArgs &A, const int64_t bid) {
+// Workgroup `bid` of one side's item pass.  PARTS: the owner rows are sums of
+// x_parts parts (see launch_item_pass_parts).
+template <int K, int V, bool BF16, bool LOSS_ONLY, bool BUF, bool PE, bool PARTS = false>
+__device__ __forceinline__ void item_pass_group(const PassArgs &A, const int64_t bid, const int32_t x_parts = 0) {
     constexpr int G = K / V;
     constexpr int NG = 64 / G;
     static_assert(G >= 1 && G <= 16 && (G & (G - 1)) == 0, "group must fit a DPP row");
@@ -481,7 +482,19 @@ __device__ __forceinline__ void item_pass_group(const PassArgs &A, const int64_t
         beg = rb + q * deg / parts;
         end = rb + (q + 1) * deg / parts;
         const int64_t orow = A.owner_mod ? row % A.owner_mod : row;
-        load_coords<G, V, BF16>(A.X + orow * K, lg, x);
+        if constexpr (PARTS) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) x[v] = 0.f;
+#pragma unroll 4
+            for (int32_t j = 0; j < x_parts; ++j) {
+                float part[V];
+                load_coords<G, V, BF16>(A.X + (orow * x_parts + j) * K, lg, part);
+#pragma unroll
+                for (int v = 0; v < V; ++v) x[v] += part[v];
+            }
+        } else {
+            load_coords<G, V, BF16>(A.X + orow * K, lg, x);
+        }
     } else {
 #pragma unroll
         for (int v = 0; v < V; ++v) x[v] = 0.f;
@@ -580,6 +593,11 @@ __device__ __forceinline__ void item_pass_group(const PassArgs &A, const int64_t
 template <int K, int V, bool BF16, bool LOSS_ONLY, bool BUF, bool PE = false>
 __global__ __launch_bounds__(kThreads) TSID_OCCUPANCY void k_item_pass(const PassArgs A) {
     item_pass_group<K, V, BF16, LOSS_ONLY, BUF, PE>(A, blockIdx.x);
+}
+
+template <int K, int V, bool BUF>
+__global__ __launch_bounds__(kThreads) TSID_OCCUPANCY void k_item_pass_parts(const PassArgs A, const int32_t x_parts) {
+    item_pass_group<K, V, false, false, BUF, false, true>(A, blockIdx.x, x_parts);
 }
 
 // Both passes of a simultaneous step in one launch: the Q pass reads only the
@@ -1126,6 +1144,22 @@ void item_pass_kv(bool loss_only, const PassArgs &a, hipStream_t s, hipEvent_t e
 }
 
 template <int K, int V, bool BF16>
+void item_pass_parts_kv(const PassArgs &a, int32_t x_parts, hipStream_t s) {
+    if constexpr (BF16) {
+        fail(TSID_E_INVAL, "rows in parts are fp32");
+    } else {
+        constexpr int NG = 64 / (K / V);
+        const int grid = ceil_div(a.n_items, (int64_t)kWaves * NG);
+        if (grid <= 0) return;
+        if (a.y_rows * (int64_t)K * 4 < (int64_t(1) << 31))
+            hipLaunchKernelGGL((k_item_pass_parts<K, V, true>), dim3(grid), dim3(kThreads), 0, s, a, x_parts);
+        else
+            hipLaunchKernelGGL((k_item_pass_parts<K, V, false>), dim3(grid), dim3(kThreads), 0, s, a, x_parts);
+        TSID_HIP(hipGetLastError());
+    }
+}
+
+template <int K, int V, bool BF16>
 void item_pass_sched_kv(const PassArgs &a, const int32_t *sched, int64_t n_wg, hipStream_t s, hipEvent_t ev0,
                         hipEvent_t ev1) {
     if (n_wg <= 0) return;
@@ -1264,6 +1298,11 @@ void fixup_kv(const PassArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) 
 void launch_item_pass(int K, int prec, bool loss_only, const PassArgs &a, hipStream_t s,
                       hipEvent_t ev0, hipEvent_t ev1) {
     TSID_DISPATCH_K(K, item_pass_kv, loss_only, a, s, ev0, ev1)
+}
+
+void launch_item_pass_parts(int K, const PassArgs &a, int32_t x_parts, hipStream_t s) {
+    const int prec = TSID_FP32;
+    TSID_DISPATCH_K(K, item_pass_parts_kv, a, x_parts, s)
 }
 
 void launch_item_pass_pair(int K, int prec, const PassArgs &a0, const PassArgs &a1, hipStream_t s, hipEvent_t ev0,

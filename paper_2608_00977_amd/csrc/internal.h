@@ -198,6 +198,10 @@ void launch_item_pass_sched(int K, int prec, const PassArgs &a, const int32_t *s
 int items_per_workgroup(int K, int prec);
 void launch_item_pass(int K, int prec, bool loss_only, const PassArgs &a, hipStream_t s,
                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// The fp32 pass over owner rows that are sums of x_parts parts each (row x:
+// a.X + x * x_parts * K ..; zero rows for x_parts = 0), added in order.  Not
+// loss-only, no clip 2.
+void launch_item_pass_parts(int K, const PassArgs &a, int32_t x_parts, hipStream_t s);
 // The P pass (a0) and the Q pass (a1) of one simultaneous step in one launch
 // (full-gradient, not loss-only; two launches if the sides' gathers differ).
 void launch_item_pass_pair(int K, int prec, const PassArgs &a0, const PassArgs &a1, hipStream_t s,
@@ -367,6 +371,7 @@ struct AdamArgs {
     int64_t n_items_ub;
     int32_t E;
     float *carry;
+    int32_t items_per_wave;
     int64_t n_fixed;
 };
 bool adam_supported(int K);
