@@ -265,6 +265,8 @@ struct tsid_ctx {
     std::string err;
     int32_t *err_dev = nullptr;      // error slots of build / fit / loss
     int32_t *err_host = nullptr;     // pinned mirror
+    double *small_host = nullptr;    // pinned: a small fit's loss history, written by its kernel
+    int32_t small_cap = 0;
     Template *tpl = nullptr;
     int32_t epochs_done = 0;         // of the last fit
     int32_t timing = 0;              // time every timing-th epoch (0: off)
@@ -1863,6 +1865,78 @@ void fit_minibatch(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, doub
                                    std::to_string(s_fail % B));
 }
 
+// Whether a fit runs as one workgroup (k_fit_small): fp32 full-gradient epochs
+// under the automatic modes with nothing to time, factors and cells in one
+// compute unit's LDS, and an epoch there shorter than the launches that it
+// replaces (8 us at least).  What an epoch there takes grows with the cells of a
+// group's share plus those of the longest bucket, which one group walks, at
+// about 150 ns each (fp64 sums).  40 epochs and the call, launches -> one
+// workgroup: 200 x 160 rows, 1,440 cells, k = 8 (23 such cells) 352 -> 176 us; 600
+// x 500 rows, 4,000 cells, k = 8 (38) 345 -> 349 us; 300 x 250 rows, 5,000 cells,
+// k = 16 (71) 461 -> 582 us; 120 x 100 rows, 3,000 cells, k = 32 (94) 737 -> 585 us.
+#ifndef TSID_SMALL_CELLS
+#define TSID_SMALL_CELLS 32
+#endif
+bool fit_is_small(const tsid_ctx *c, const tsid_fit_opts *o) {
+    const Template &t = *c->tpl;
+    if (o->prec != TSID_FP32 || o->clip == 2 || o->epochs < 1 || t.sim.on || c->timing ||
+        c->pass_kernel != TSID_PASS_AUTO || c->dense_fill > 0.f || c->row_blocks > 1 || t.m_t < 1 || t.n_t < 1 ||
+        t.k > 64)  // k = 128: an epoch of the kernel spills, 60 x 60 rows, 1,200 cells: 446 -> 812 us
+        return false;
+    // pinned memory holds the history; a run of more epochs takes the launches
+    if (o->epochs > (1 << 16)) return false;
+    if (t.nnz > INT32_MAX / 2 || fit_small_lds(t.k, t.m_t, t.n_t, t.nnz) > kSmallFitLds) return false;
+    int64_t most = 0;
+    for (const auto &ptr : t.hptr)
+        for (size_t x = 0; x + 1 < ptr.size(); ++x) most = std::max(most, ptr[x + 1] - ptr[x]);
+    return 2 * t.nnz / fit_small_groups(t.k) + most <= TSID_SMALL_CELLS;
+}
+
+void fit_small(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *loss_hist) {
+    Template &t = *c->tpl;
+    const int32_t T = o->epochs;
+    if (c->small_cap < T + 2) {
+        if (c->small_host) (void)hipHostFree(c->small_host);
+        c->small_host = nullptr;
+        c->small_cap = 0;
+        const int32_t cap = std::max(T + 2, 1024);
+        TSID_HIP(hipHostMalloc((void **)&c->small_host, (size_t)cap * sizeof(double), hipHostMallocDefault));
+        c->small_cap = cap;
+    }
+    c->dense_used = tsid_dense_info{};
+    // the pass that the automatic rule names; the arithmetic is the same
+    for (int sd = 0; sd < 2; ++sd)
+        c->used_kernel[sd] = slab_wanted(c, sd, o->prec) ? TSID_PASS_SLAB : TSID_PASS_ITEM;
+    c->used_blocks = 1;
+    c->epochs_done = 0;
+    SmallFitArgs a{};
+    a.stream_r = t.stream_r;
+    a.stream_c = t.stream_c;
+    a.row_ptr = t.row_ptr;
+    a.col_ptr = t.col_ptr;
+    a.m = t.m_t;
+    a.n = t.n_t;
+    a.nnz = (int32_t)t.nnz;
+    a.epochs = T;
+    a.P = P;
+    a.Q = Q;
+    a.loss = loss_hist ? c->small_host : nullptr;
+    a.done = c->err_host;
+    a.lam = o->lambda;
+    a.lr = o->lr;
+    a.xi = o->clip_xi;
+    a.clip = o->clip;
+    a.degree_r = side_scaled(o->step, 0);
+    a.degree_c = side_scaled(o->step, 1);
+    launch_fit_small(t.k, a, c->comp);
+    TSID_HIP(hipStreamSynchronize(c->comp));
+    const int32_t last = c->err_host[0];
+    c->epochs_done = last;
+    if (loss_hist)
+        for (int ep = 0; ep <= T; ++ep) loss_hist[ep] = ep <= last ? c->small_host[ep] : NAN;
+    if (last < T) fail(TSID_E_NONFINITE, "non-finite update in epoch " + std::to_string(last));
+}
+
 void fit(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *loss_hist) {
     if (!c->tpl) fail(TSID_E_STATE, "no template: call tsid_build_template first");
     check_opts(o);
@@ -1879,6 +1953,7 @@ void fit(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *loss_h
         if (c->pass_kernel == TSID_PASS_SLAB) fail(TSID_E_INVAL, "the similarity term runs on the item pass");
     }
     if (c->mb_batches > 0) return fit_minibatch(c, P, Q, o, loss_hist);
+    if (fit_is_small(c, o)) return fit_small(c, P, Q, o, loss_hist);
     ensure_fit_buffers(c, o->prec, o->epochs, o->clip != 2, 0, o->clip == 2 || sim.on);
     const int32_t nb = ensure_qblock(c, o->prec);  // row blocks of the Q pass (1: one pass)
     c->used_blocks = nb;
@@ -2671,6 +2746,7 @@ void tsid_destroy(tsid_ctx *c) {
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     c->arena.release(c->err_dev);
     if (c->err_host) (void)hipHostFree(c->err_host);
+    if (c->small_host) (void)hipHostFree(c->small_host);
     if (c->h2d) (void)hipStreamDestroy(c->h2d);
     if (c->d2h) (void)hipStreamDestroy(c->d2h);
     if (c->own_comp && c->comp) (void)hipStreamDestroy(c->comp);

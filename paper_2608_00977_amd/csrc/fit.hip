@@ -1054,6 +1054,139 @@ __global__ __launch_bounds__(64 * WAVES) void k_extend_group(const PassArgs A, i
     }
 }
 
+// Lane group sums in fp64 (as group_sum).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)dpp_i<CTRL>((int)(uint32_t)u), hi = (uint32_t)dpp_i<CTRL>((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int G>
+__device__ __forceinline__ double group_sum_f64(double x) {
+    if constexpr (G >= 2) x += dpp_f64<0xB1>(x);
+    if constexpr (G >= 4) x += dpp_f64<0x4E>(x);
+    if constexpr (G >= 8) x += dpp_f64<0x141>(x);
+    if constexpr (G >= 16) x += dpp_f64<0x140>(x);
+    return x;
+}
+
+// A whole fp32 fit in one launch, for templates that fit one compute unit's LDS
+// (factors twice, both streams, the bucket pointers): one workgroup runs every
+// epoch, a lane group of K / V lanes per owner row, with one barrier per epoch
+// where separate launches would be.  Such a fit is bound by launches otherwise:
+// 200 x 160 rows, 1,440 cells, k = 8, 50 epochs: 405 us a call with two launches
+// an epoch and the history's reductions, 210 us in one launch, which writes
+// the history straight to pinned host memory.  An epoch is bound by the latency
+// of its longest bucket's walk through LDS, so the sums are fp64 at little cost:
+// epochs of the plain step amplify a rounding up to a few tens of times, and
+// sums in fp32 in this order left the history of a case 1.2e-6 off where the two
+// launches leave it 1.7e-7 off.  With fp64 sums the mean error over 36 templates
+// and 50 epochs against 64 bits is 1.9e-7 (factors) and 7.3e-8 (history), the
+// launches' 1.9e-7 and 8.4e-8.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64;
+template <int K, int V>
+__global__ __launch_bounds__(kSmallThreads) void k_fit_small(const SmallFitArgs A) {
+    constexpr int G = K / V;
+    constexpr int NGRP = kSmallThreads / G;
+    extern __shared__ float4 lds4[];
+    const int m = A.m, owners = A.m + A.n;
+    float *const buf = reinterpret_cast<float *>(lds4);          // 2 x owners x K: rows of P, then of Q
+    int2 *const rec = reinterpret_cast<int2 *>(buf + 2 * owners * K);  // 2 x nnz: {place of the other row, value}
+    int32_t *const ptr = reinterpret_cast<int32_t *>(rec + 2 * A.nnz);  // owners + 1
+    __shared__ double part[2][kSmallWaves];
+    __shared__ int stop[2];  // by epoch parity: one epoch reads its flag while the next may set its own
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int grp = t / G, lg = t % G;
+    if (t < 2) stop[t] = 0;
+    for (int j = t; j < m * K; j += kSmallThreads) buf[j] = A.P[j];
+    for (int j = t; j < A.n * K; j += kSmallThreads) buf[m * K + j] = A.Q[j];
+    for (int j = t; j <= m; j += kSmallThreads) ptr[j] = (int32_t)A.row_ptr[j];
+    for (int j = t; j < A.n; j += kSmallThreads) ptr[m + 1 + j] = A.nnz + (int32_t)A.col_ptr[j + 1];
+    for (int j = t; j < A.nnz; j += kSmallThreads) {
+        const int2 r = A.stream_r[j], c = A.stream_c[j];
+        rec[j] = make_int2((m + r.x) * K, r.y);
+        rec[A.nnz + j] = make_int2(c.x * K, c.y);
+    }
+    __syncthreads();
+    int ep = 0;
+    for (;; ++ep) {
+        const bool last = ep == A.epochs;  // the loss of the last iterate only
+        if (last && !A.loss) break;
+        const float *cur = buf + (ep & 1) * owners * K;
+        float *nxt = buf + ((ep & 1) ^ 1) * owners * K;
+        double sum = 0.0;
+        for (int o = grp; o < owners; o += NGRP) {
+            float x[V];
+            load_coords<G, V, false>(cur + o * K, lg, x);
+            double acc[V], e2 = 0.0, nrm = 0.0;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                acc[v] = 0.0;
+                nrm = fma((double)x[v], (double)x[v], nrm);
+            }
+            const int b0 = ptr[o], b1 = ptr[o + 1];
+            if (!last || o < m) {
+                // four cells' records, then their rows, in flight
+                for (int j = b0; j < b1; j += 4) {
+                    int2 r[4];
+                    float y[4][V];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r[i] = rec[j + i < b1 ? j + i : b1 - 1];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) load_coords<G, V, false>(cur + r[i].x, lg, y[i]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        double d = 0.0;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) d = fma((double)x[v], (double)y[i][v], d);
+                        const double e =
+                            j + i < b1 ? (double)__int_as_float(r[i].y) - group_sum_f64<G>(d) : 0.0;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) acc[v] = fma(e, (double)y[i][v], acc[v]);
+                        e2 = fma(e, e, e2);
+                    }
+                }
+            }
+            nrm = group_sum_f64<G>(nrm);
+            if (lg == 0) sum += (o < m ? e2 : 0.0) + (double)A.lam * nrm;
+            if (!last) {
+                const bool scaled = o < m ? A.degree_r : A.degree_c;
+                const double s = scaled ? 1.0 / (double)(b1 - b0 > 1 ? b1 - b0 : 1) : 1.0;
+                bool bad = false;
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    // clipped_step in fp64
+                    const double down = 2.0 * acc[v] - 2.0 * (double)A.lam * (double)x[v];
+                    double d = A.clip == 3 ? down : s * down;
+                    if (A.clip && d > (double)A.xi) d = (double)A.xi;
+                    if (A.clip == 3) d *= s;
+                    x[v] = (float)fma((double)A.lr, d, (double)x[v]);
+                    bad |= !__builtin_isfinite(x[v]);
+                }
+                store_coords<G, V, false>(nxt + o * K, lg, x);
+                if (bad) stop[ep & 1] = 1;
+            }
+        }
+        if (A.loss) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+            if (lane == 0) part[ep & 1][wv] = sum;
+        }
+        __syncthreads();
+        if (A.loss && t == 0) {
+            double l = 0.0;
+            for (int w = 0; w < kSmallWaves; ++w) l += part[ep & 1][w];
+            A.loss[ep] = l;
+        }
+        if (last || stop[ep & 1]) break;  // a non-finite update: this epoch's factors stay
+    }
+    const float *fin = buf + (ep & 1) * owners * K;
+    for (int j = t; j < m * K; j += kSmallThreads) A.P[j] = fin[j];
+    for (int j = t; j < A.n * K; j += kSmallThreads) A.Q[j] = fin[m * K + j];
+    if (t == 0) *A.done = ep;
+}
+
 template <int K>
 __global__ void k_row_norms(const float *X, int32_t rows, float *norm) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1383,6 +1516,34 @@ void launch_to_bf16(const float *X, int64_t n, uint16_t *Xb, hipStream_t s) {
     int64_t g = (n + 255) / 256;
     k_to_bf16<<<(int)(g > 65536 ? 65536 : g), 256, 0, s>>>(X, n, Xb);
     TSID_HIP(hipGetLastError());
+}
+
+namespace {
+template <int K, int V>
+void fit_small_k(const SmallFitArgs &a, size_t lds, hipStream_t s) {
+    TSID_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_fit_small<K, V>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallFitLds));
+    hipLaunchKernelGGL((k_fit_small<K, V>), dim3(1), dim3(kSmallThreads), lds, s, a);
+    TSID_HIP(hipGetLastError());
+}
+}  // namespace
+
+size_t fit_small_lds(int K, int64_t m, int64_t n, int64_t nnz) {
+    return (size_t)(2 * (m + n) * K * 4 + 2 * nnz * 8 + (m + n + 1) * 4);
+}
+
+int fit_small_groups(int K) { return kSmallThreads / (K / 4); }
+
+void launch_fit_small(int K, const SmallFitArgs &a, hipStream_t s) {
+    const size_t lds = fit_small_lds(K, a.m, a.n, a.nnz);
+    if (lds > kSmallFitLds) fail(TSID_E_INVAL, "the template does not fit one workgroup");
+    switch (K) {
+        case 8: fit_small_k<8, 4>(a, lds, s); break;
+        case 16: fit_small_k<16, 4>(a, lds, s); break;
+        case 32: fit_small_k<32, 4>(a, lds, s); break;
+        case 64: fit_small_k<64, 4>(a, lds, s); break;
+        default: fail(TSID_E_INVAL, "unsupported rank");
+    }
 }
 
 size_t reduce_scratch_elems(int n_slots) { return (size_t)kRedTerms * kRedBlocks * (n_slots > 0 ? n_slots : 1); }

@@ -246,6 +246,24 @@ void launch_loss_reduce(const float *e2, int64_t e2_stride, int64_t ne, const fl
                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const float *ns = nullptr,
                         int64_t nns = 0, double w4 = 0.0);
 
+// A whole fp32 full-gradient fit by one workgroup (clip 0, 1 or 3): P and Q in
+// place, L(P_t, Q_t) to loss[t] for t = 0 .. epochs (or null), and the epochs
+// done to *done (loss and done may be host memory that the device can write).
+struct SmallFitArgs {
+    const int2 *stream_r, *stream_c;
+    const int64_t *row_ptr, *col_ptr;
+    int32_t m, n, nnz, epochs;
+    float *P, *Q;
+    double *loss;
+    int32_t *done;
+    float lam, lr, xi;
+    int32_t clip, degree_r, degree_c;
+};
+constexpr size_t kSmallFitLds = 150 * 1024;  // dynamic LDS; the rest is the kernel's own
+size_t fit_small_lds(int K, int64_t m, int64_t n, int64_t nnz);
+int fit_small_groups(int K);  // owner rows the workgroup takes at a time
+void launch_fit_small(int K, const SmallFitArgs &a, hipStream_t s);
+
 // Multi-view similarity term (similarity.hip): for every template column i,
 // gs[i] = sum_e S_e (q_i - q_col[e]) and se[i] = sum_e S_e ||q_i - q_col[e]||^2
 // over the entries e of row i of S (CSR ptr / col / val), from fp32 Q.  se
