@@ -208,6 +208,9 @@ void launch_item_pass_pair(int K, int prec, const PassArgs &a0, const PassArgs &
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_fixup(int K, int prec, const PassArgs &a, hipStream_t s, hipEvent_t ev0 = nullptr,
                   hipEvent_t ev1 = nullptr);
+// Both sides' fixups of one simultaneous step in one launch.
+void launch_fixup_pair(int K, int prec, const PassArgs &a0, const PassArgs &a1, hipStream_t s,
+                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // Row blocks of a bucketed stream: bounds[j * rows + x] = first cell of bucket
 // x whose other index is >= row_bounds[j], for j = 0 .. n_blocks (int64;
 // row_bounds holds n_blocks + 1 nondecreasing device values).
