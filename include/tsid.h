@@ -194,8 +194,8 @@ tsid_status tsid_loss_noalloc(tsid_ctx *ctx, const float *P, const float *Q, flo
  * takes opts->epochs gradient steps of Eq. 5 (opts->step, opts->clip apply;
  * opts->prec is ignored: the fixed side is read in fp32).  A row's steps are
  * taken in one of two forms with the same result up to rounding:
- *  - per cell, with the template fit's residual/gradient kernel, in fp32,
- *    gathering the row's fixed factors once per step;
+ *  - per cell, in fp32, the row's fixed factors gathered once into registers
+ *    (rows beyond a workgroup's registers gather them once per step);
  *  - in Gram form, for rows of at least a threshold number of cells: the
  *    gradient 2 lambda x - 2 (b - G x) from G = sum p p^T and b = sum r p,
  *    accumulated once in fp64 on the matrix cores, with the steps in fp64.
@@ -315,6 +315,9 @@ tsid_status tsid_sync(tsid_ctx *ctx);
  *                  k <= 64, holds on average at least 4 cells per staged row
  *                  and block of 512 rows, and has no bucket longer than twice
  *                  the mean plus 64; the item pass otherwise.
+ *                  A small fp32 fit (k <= 64, factors and streams within 150
+ *                  KB, short buckets) runs in one workgroup and reports the
+ *                  kernels that this rule names; its sums are fp64.
  * Takes effect at the next tsid_fit_template.  Errors: E_INVAL (unknown mode);
  * a fit with TSID_PASS_SLAB on an unsupported rank or precision returns
  * E_INVAL. */
