@@ -73,7 +73,13 @@ __device__ __forceinline__ void load_quarter(const float *p, float (&x)[KQ]) {
 //  2. The Adam step on those four (16-byte loads and stores of C, M and V).
 //  3. X += C_tile B_tile: the four coefficients are the A operands as they
 //     stand, operand j covering basis lines 4 q + j.
-// The waves' partial products are added in wave order through LDS.  What bounds
+// The waves' partial products are added in wave order through LDS.  fp32 sums
+// in long chains lose digits, so S takes four chains of K / 4 coordinates and
+// each tile's part of X a chain of its own: errors against 64 bits at k = 64,
+// 1,024 basis lines, 8.4e-8 (S) and 4.9e-8 (X), where two chains of K / 2 and one
+// chain of 64 basis lines left 1.07e-7 and 6.4e-8.  At k = 64 three waves a SIMD
+// need the register cap (47.2 us a step of 1,000 lines x 4,096 basis lines; 49.1
+// with two).  What bounds
 // it: the coefficients' and moments' 24 bytes each way per coefficient and step
 // (they stay in the memory-side cache), and the latency of a tile's chain of
 // loads, product, step, product.  500 free lines x 4,096 basis lines at k = 64:
@@ -81,7 +87,7 @@ __device__ __forceinline__ void load_quarter(const float *p, float (&x)[KQ]) {
 // shuffles, before); 8 waves of two tiles each instead of 4 of four, more waves
 // in flight without the two tiles in turn, took 25 us.
 template <int K, bool FIRST>
-__global__ __launch_bounds__(64 * kAdamUpdWaves) void k_adam_update(const AdamArgs A, float c1, float c2) {
+__global__ __launch_bounds__(64 * kAdamUpdWaves, K == 64 ? 3 : 1) void k_adam_update(const AdamArgs A, float c1, float c2) {
     constexpr int KQ = K / 4;             // coordinates per lane in step 1
     constexpr int NX = (K + 15) / 16;     // 16-coordinate blocks of step 3
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -162,13 +168,14 @@ __global__ __launch_bounds__(64 * kAdamUpdWaves) void k_adam_update(const AdamAr
 #pragma unroll
     for (int i = 0; i < KQ; ++i) gv[i] *= -2.f;  // dL/dx_f = -2 sum_e e p
     auto step = [&](int64_t l0, Tile &T) {
-        f4v st = f4v{0.f, 0.f, 0.f, 0.f}, su = st;  // two chains of products
+        constexpr int NS = KQ < 4 ? KQ : 4;  // chains of the dot product, of K / 4 terms at most (k = 8: 4)
+        f4v sc[NS];
 #pragma unroll
-        for (int i = 0; i < KQ; i += 2) {
-            st = __builtin_amdgcn_mfma_f32_16x16x4f32(T.b[i], gv[i], st, 0, 0, 0);
-            su = __builtin_amdgcn_mfma_f32_16x16x4f32(T.b[i + 1], gv[i + 1], su, 0, 0, 0);
-        }
-        st += su;
+        for (int i = 0; i < NS; ++i) sc[i] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < KQ; ++i) sc[i % NS] = __builtin_amdgcn_mfma_f32_16x16x4f32(T.b[i], gv[i], sc[i % NS], 0, 0, 0);
+        f4v st = sc[0] + sc[1];
+        if constexpr (NS == 4) st += sc[2] + sc[3];
         float cn[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -196,6 +203,9 @@ __global__ __launch_bounds__(64 * kAdamUpdWaves) void k_adam_update(const AdamAr
                     }
             }
         }
+        f4v xt[NX];  // this tile's product, a chain of 16 terms
+#pragma unroll
+        for (int nb = 0; nb < NX; ++nb) xt[nb] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool in = l0 + 4 * q + j < A.n_b;
@@ -203,8 +213,10 @@ __global__ __launch_bounds__(64 * kAdamUpdWaves) void k_adam_update(const AdamAr
             if (!in) cn[j] = 0.f;  // lines past the basis add nothing
 #pragma unroll
             for (int nb = 0; nb < NX; ++nb)
-                xa[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cn[j], T.bx[nb][j], xa[nb], 0, 0, 0);
+                xt[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cn[j], T.bx[nb][j], xt[nb], 0, 0, 0);
         }
+#pragma unroll
+        for (int nb = 0; nb < NX; ++nb) xa[nb] += xt[nb];
     };
     for (int i = 0; i < 4; i += 2) {
         const int64_t l0 = first + 16 * i;
