@@ -8,7 +8,7 @@
 // The coefficients move by the Adam method (bias-corrected first and second
 // moment estimates, elementwise step lr m^ / (sqrt(w^) + eps)), from C = 0.
 //
-// A step is two launches, free lines being independent:
+// A step is two launches (three with long lines), free lines being independent:
 //  the item pass  the residual of every entry of f and sum_e e p, with x_f as
 //                 the owner row (the sum of the previous step's partial
 //                 products, in slice order) and F the gathered table: the
@@ -154,14 +154,16 @@ __global__ __launch_bounds__(64 * kAdamUpdWaves, K == 64 ? 3 : 1) void k_adam_up
     } else {
 #pragma unroll
         for (int i = 0; i < KQ; ++i) gv[i] = 0.f;
+        // a partial sum keeps the pass's lane order
+        constexpr int W = KQ < 4 ? KQ : 4;  // neighbours in both orders
         for (uint32_t it = i0; it < i1; it = (it / ng + 1) * ng) {
             const float *p = A.carry + (int64_t)it * K;
 #pragma unroll
-            for (int i = 0; i < KQ; ++i) {
-                // the sums keep the pass's lane order: at k = 128 lane g of 16
-                // holds chunks g and g + 16 of four coordinates
-                const int at = K == 128 ? ((8 * (q & 1) + i / 4) * 8 + (q / 2) * 4 + i % 4) : q * KQ + i;
-                gv[i] += p[at];
+            for (int i = 0; i < KQ; i += W) {
+                float part[W];
+                load_quarter<W>(p + ItemLanes<K>::place(q * KQ + i), part);
+#pragma unroll
+                for (int j = 0; j < W; ++j) gv[i + j] += part[j];
             }
         }
     }
@@ -273,15 +275,28 @@ void adam_k(const AdamArgs &a, int32_t steps, hipStream_t st) {
     g.epoch = INT32_MAX;  // skipped once any step has stored a non-finite flag
     g.skip_after_nonfinite = a.skip_after_nonfinite;
     g.partial_out = a.gt;
+    // The update's workgroups add the partial sums of lines that span waves
+    // themselves, every slice and wave anew, which saves a launch; past 16 MB of such
+    // reads, or 32 sums a line (each is a dependent round of the line's chain), one
+    // fixup launch is the cheaper one.  us a step, without -> with it: k = 64, 100
+    // lines of 5,000 cells, 16 / 64 / 512 slices 39.7 -> 42.2 / 60.5 -> 53.1 / 269
+    // -> 187; of 20,000 cells, 4 / 512 slices 97 -> 91 / 718 -> 310; k = 128, 1,000
+    // lines of 640 cells, 4 / 16 slices 49.4 -> 52.8 / 101.2 -> 98.6, 100 of 20,000
+    // cells, 4 slices 196 -> 156.
+    const int64_t sums = (a.n_items_ub - a.n_free) / a.items_per_wave;
+    const bool fix = sums * a.n_slices * K > (int64_t(4) << 20) || sums > 32 * a.n_free;
+    AdamArgs u = a;
+    if (fix) u.items_per_wave = INT32_MAX;  // every line's sum is in gt
     for (int32_t t = 1; t <= steps; ++t) {
         b1t *= b1;
         b2t *= b2;
         const float c1 = (float)(1.0 / (1.0 - b1t)), c2 = (float)(1.0 / (1.0 - b2t));
         launch_item_pass_parts(K, g, t == 1 ? 0 : a.n_slices, st);
+        if (fix) launch_fixup(K, TSID_FP32, g, st);
         if (t == 1)
-            hipLaunchKernelGGL((k_adam_update<K, true>), gu, dim3(64 * kAdamUpdWaves), 0, st, a, c1, c2);
+            hipLaunchKernelGGL((k_adam_update<K, true>), gu, dim3(64 * kAdamUpdWaves), 0, st, u, c1, c2);
         else
-            hipLaunchKernelGGL((k_adam_update<K, false>), gu, dim3(64 * kAdamUpdWaves), 0, st, a, c1, c2);
+            hipLaunchKernelGGL((k_adam_update<K, false>), gu, dim3(64 * kAdamUpdWaves), 0, st, u, c1, c2);
         TSID_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_adam_x<K>, dim3(gx), dim3(256), 0, st, a, steps > 0 ? a.n_slices : 0);

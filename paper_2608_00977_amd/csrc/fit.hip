@@ -126,21 +126,6 @@ __device__ __forceinline__ void store_f32(float *p, const float (&x)[V]) {
     for (int c = 0; c < V / 4; ++c) q[c] = make_float4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
 }
 
-// The coordinates a lane holds.  A row of the gathered table is read in
-// 16-byte chunks (Q coordinates: 8 in bf16, 4 in fp32); lane lg of a group of
-// G lanes holds V / Q of them, its n-th being chunk n G + lg of the row, so
-// that one gather instruction of a group reads G * 16 consecutive bytes
-// (whole 128-byte lines at G = 8) instead of a strided part of every line of
-// the row.  Element n Q + j of a lane's arrays is coordinate coord(lg, n) + j;
-// with one chunk per lane this is the plain split lg V .. lg V + V - 1.
-template <int G, int V, bool BF16>
-struct Lanes {
-    static constexpr int Q = BF16 ? 8 : 4;
-    static constexpr int N = V / Q;
-    static_assert(V % Q == 0, "a lane holds whole 16-byte chunks");
-    static __device__ __forceinline__ int coord(int lg, int n) { return (n * G + lg) * Q; }
-};
-
 // This lane's coordinates of an fp32 row (row points at coordinate 0).
 template <int G, int V, bool BF16>
 __device__ __forceinline__ void load_coords(const float *row, int lg, float (&x)[V]) {
@@ -1423,30 +1408,6 @@ void fixup_pair_kv(const PassArgs &a0, const PassArgs &a1, hipStream_t s, hipEve
 
 }  // namespace
 
-// Coordinates per lane (V) for each rank: a cell is handled by G = K / V
-// lanes.  Smaller G means fewer DPP and swizzle steps per cell; larger G means
-// fewer distinct rows per gather instruction.
-#ifndef TSID_V_F32_8
-#define TSID_V_F32_8 4
-#endif
-#ifndef TSID_V_F32_16
-#define TSID_V_F32_16 4
-#endif
-#ifndef TSID_V_F32_32
-#define TSID_V_F32_32 4
-#endif
-#ifndef TSID_V_F32_64
-#define TSID_V_F32_64 4
-#endif
-#ifndef TSID_V_F32_128
-#define TSID_V_F32_128 8
-#endif
-#ifndef TSID_V_BF16_64
-#define TSID_V_BF16_64 8
-#endif
-#ifndef TSID_V_BF16_128
-#define TSID_V_BF16_128 16
-#endif
 #define TSID_DISPATCH_K(K_, FN, ...)                                                              \
     switch (K_) {                                                                                 \
         case 8: prec ? FN<8, 8, true>(__VA_ARGS__) : FN<8, TSID_V_F32_8, false>(__VA_ARGS__); break; \

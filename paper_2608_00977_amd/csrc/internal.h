@@ -43,6 +43,56 @@ __device__ __forceinline__ float clipped_step(float g, float s, int32_t clip, fl
     return d;
 }
 
+// Coordinates per lane (V) for each rank: a cell is handled by G = K / V
+// lanes.  Smaller G means fewer DPP and swizzle steps per cell; larger G means
+// fewer distinct rows per gather instruction.
+#ifndef TSID_V_F32_8
+#define TSID_V_F32_8 4
+#endif
+#ifndef TSID_V_F32_16
+#define TSID_V_F32_16 4
+#endif
+#ifndef TSID_V_F32_32
+#define TSID_V_F32_32 4
+#endif
+#ifndef TSID_V_F32_64
+#define TSID_V_F32_64 4
+#endif
+#ifndef TSID_V_F32_128
+#define TSID_V_F32_128 8
+#endif
+#ifndef TSID_V_BF16_64
+#define TSID_V_BF16_64 8
+#endif
+#ifndef TSID_V_BF16_128
+#define TSID_V_BF16_128 16
+#endif
+
+// The coordinates a lane holds.  A row of the gathered table is read in
+// 16-byte chunks (Q coordinates: 8 in bf16, 4 in fp32); lane lg of a group of
+// G lanes holds V / Q of them, its n-th being chunk n G + lg of the row, so
+// that one gather instruction of a group reads G * 16 consecutive bytes
+// (whole 128-byte lines at G = 8) instead of a strided part of every line of
+// the row.  Element n Q + j of a lane's arrays is coordinate coord(lg, n) + j;
+// with one chunk per lane this is the plain split lg V .. lg V + V - 1.
+template <int G, int V, bool BF16>
+struct Lanes {
+    static constexpr int Q = BF16 ? 8 : 4;
+    static constexpr int N = V / Q;
+    static_assert(V % Q == 0, "a lane holds whole 16-byte chunks");
+    static __device__ __forceinline__ int coord(int lg, int n) { return (n * G + lg) * Q; }
+    // Where coordinate x stands when the lanes' arrays follow one another (the
+    // partial sums that a wave leaves); the chunk of Q that holds it stays together.
+    static __device__ __forceinline__ int place(int x) { return x / Q % G * V + x / Q / G * Q + x % Q; }
+};
+
+// The lanes of the fp32 item pass at rank K.
+template <int K>
+constexpr int kItemV = K == 8 ? TSID_V_F32_8 : K == 16 ? TSID_V_F32_16 : K == 32 ? TSID_V_F32_32
+                     : K == 64 ? TSID_V_F32_64 : TSID_V_F32_128;
+template <int K>
+using ItemLanes = Lanes<K / kItemV<K>, kItemV<K>, false>;
+
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 inline int bits_for(int64_t count) {  // bits to hold values 0..count-1 (at least 1)
     int b = 1;
