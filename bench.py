@@ -408,6 +408,7 @@ def main():
         sparse_nnz = int(bp[m_t] - bp[0])
     avg = [tm["pass_ms"][j] / max(1, tm["pass_launches"][j]) for j in range(2)]
     src_of = {"item": "fit.hip", "slab": "slab.hip"}
+    small = kernels[0] == "small"  # the whole fit in one launch: every epoch is timed
     cand = []
 
     def add(ms, by_fl, name, desc, src, which, kind, units):
@@ -423,8 +424,13 @@ def main():
             by_ -= owners * 4 * k
         return by_, fl_
 
-    pair = kernels[0] == kernels[1] and tm["pass_launches"][1] == 0 and tm["pass_launches"][0] > 0
-    if pair:  # both passes in one launch (timed as the P pass; no Q pass launch)
+    pair = kernels[0] == kernels[1] and tm["pass_launches"][1] == 0 and tm["pass_launches"][0] > 0 and not small
+    if small:
+        per_launch = tm["epochs"] / max(1, tm["pass_launches"][0])
+        by_, fl_ = algorithmic(nnz, m_t + n_t, k, p.prec, 2)
+        add(avg[0], (by_ * per_launch, fl_ * per_launch), "k_fit_small", "all epochs of the fit", "fit.hip", "fit",
+            "small", ("hbm", "alu"))
+    elif pair:  # both passes in one launch (timed as the P pass; no Q pass launch)
         add(avg[0], pass_alg(0, 2), f"k_{kernels[0]}_pass_pair", "P and Q passes", src_of[kernels[0]], "pq_pass",
             kernels[0], ("hbm", "alu"))
     else:
@@ -520,7 +526,8 @@ def main():
         "launches": launches,
         "device_epoch_ms": tm["epoch_ms"] / max(1, tm["epochs"]),
         "timed_epochs": tm["epochs"],
-        "kernel_ms_per_epoch": {**({"pq_pass": avg[0]} if pair else {"p_pass": avg[0], "q_pass": avg[1]}),
+        "kernel_ms_per_epoch": {**({"fit": tm["epoch_ms"] / max(1, tm["epochs"])} if small else
+                                   {"pq_pass": avg[0]} if pair else {"p_pass": avg[0], "q_pass": avg[1]}),
                                 **({"pq_dense": dense_avg[0]} if dense_pair else
                                    {"p_dense": dense_avg[0], "q_dense": dense_avg[1]}),
                                 "fixups": tm["fixup_ms"] / max(1, tm["epochs"]),

@@ -315,18 +315,25 @@ tsid_status tsid_sync(tsid_ctx *ctx);
  *                  k <= 64, holds on average at least 4 cells per staged row
  *                  and block of 512 rows, and has no bucket longer than twice
  *                  the mean plus 64; the item pass otherwise.
- *                  A small fp32 fit (k <= 64, factors and streams within 150
- *                  KB, short buckets) runs in one workgroup and reports the
- *                  kernels that this rule names; its sums are fp64.
+ *                  Small fp32 fits (k <= 64, factors and streams within 150
+ *                  KB, short buckets; full-gradient epochs, clip 0, 1 or 3, no
+ *                  similarity term, no forced dense tiles or row blocks) run
+ *                  in one workgroup and one launch (reported as
+ *                  TSID_PASS_SMALL).  Their sums are fp64, so the last bits
+ *                  differ from the other kernels', and a sum beyond fp32's
+ *                  range is no failure there while the factors stay finite.
  * Takes effect at the next tsid_fit_template.  Errors: E_INVAL (unknown mode);
  * a fit with TSID_PASS_SLAB on an unsupported rank or precision returns
  * E_INVAL. */
-enum { TSID_PASS_AUTO = 0, TSID_PASS_ITEM = 1, TSID_PASS_SLAB = 2 };
+enum {
+    TSID_PASS_AUTO = 0, TSID_PASS_ITEM = 1, TSID_PASS_SLAB = 2,
+    TSID_PASS_SMALL = 3  /* reported by tsid_fit_pass_kernels only */
+};
 tsid_status tsid_set_pass_kernel(tsid_ctx *ctx, int mode);
 
-/* Pass kernels the last tsid_fit_template ran (TSID_PASS_ITEM or
- * TSID_PASS_SLAB) for the P pass and the Q pass; 0 before any fit.  Either
- * output may be NULL.  Errors: E_INVAL (ctx NULL). */
+/* Pass kernels the last tsid_fit_template ran (TSID_PASS_ITEM, TSID_PASS_SLAB,
+ * or TSID_PASS_SMALL for both) for the P pass and the Q pass; 0 before any fit.
+ * Either output may be NULL.  Errors: E_INVAL (ctx NULL). */
 tsid_status tsid_fit_pass_kernels(const tsid_ctx *ctx, int32_t *p_pass, int32_t *q_pass);
 
 /* Dense head tiles for bf16 fits (Eqs. 2-4 evaluated on the matrix cores).
@@ -414,9 +421,10 @@ tsid_status tsid_set_similarity(tsid_ctx *ctx, const int32_t *row, const int32_t
  * The batch-major copies of the streams (8 bytes per cell and side) and the
  * batch pointers (8 bytes per batch and row or column) are built at the
  * first such fit after a template, batch-count or seed change and kept with
- * the template.  With timing on, pass_ms / fixup_ms cover the first batch's
- * passes of a timed epoch and epoch_ms the whole epoch (its loss pass
- * included).  Takes effect at the next tsid_fit_template.
+ * the template.  A batch's two passes, and its fixups, are one launch each.
+ * With timing on, pass_ms / fixup_ms cover the first batch's passes of a timed
+ * epoch, which go out one by one there (with the same bits), and epoch_ms the
+ * whole epoch (its loss pass included).  Takes effect at the next tsid_fit_template.
  * Errors: E_INVAL (ctx NULL, n_batches outside [0, TSID_MAX_BATCHES]). */
 #define TSID_MAX_BATCHES 4096
 tsid_status tsid_set_minibatch(tsid_ctx *ctx, int32_t n_batches, uint64_t seed);
@@ -459,9 +467,12 @@ tsid_status tsid_fit_row_blocks(const tsid_ctx *ctx, int32_t *n_blocks);
  *  pass_ms[0] / pass_launches[0]: the P pass (row buckets); [1]: the Q pass
  *  (column buckets).  The two passes of an epoch go out as one launch,
  *  counted in [0] ([1] stays 0), unless the Q pass runs in row blocks
- *  (tsid_set_row_blocks); the slab pass's two finishing kernels are then one
- *  launch too, counted once under fixup.  fixup: the kernels that combine
- *  partial sums after a pass (item pass: buckets longer than one wave; slab pass: blocks split
+ *  (tsid_set_row_blocks); the two sides' fixups (slab pass: finishing
+ *  kernels) are then one launch too, counted once under fixup.  A fit in one
+ *  workgroup (TSID_PASS_SMALL) is one launch for all its epochs (for every
+ *  65,536 of them), counted in [0], and all of them count as timed epochs,
+ *  whatever `every`.  fixup: the kernels that combine partial sums after a
+ *  pass (item pass: buckets longer than one wave; slab pass: blocks split
  *  over several workgroups), which also update those rows; reduce: the
  *  batched loss reductions (one per 16 epochs); dense_ms[0] / [1]: the
  *  dense-tile kernels before the P / Q pass (tsid_set_dense_tiles); when

@@ -27,7 +27,8 @@ STATUS = {0: "TSID_OK", 1: "TSID_E_INVAL", 2: "TSID_E_RANGE", 3: "TSID_E_DUP",
 OK, E_INVAL, E_RANGE, E_DUP, E_NOMEM, E_DEVICE, E_STATE, E_NONFINITE = range(8)
 FP32, BF16 = 0, 1
 STEP_SUM, STEP_DEGREE, STEP_COL_DEGREE = 0, 1, 2
-PASS_KERNEL = {"auto": 0, "item": 1, "slab": 2}
+PASS_KERNEL = {"auto": 0, "item": 1, "slab": 2}  # modes of tsid_set_pass_kernel
+PASS_RAN = {**{v: name for name, v in PASS_KERNEL.items()}, 3: "small"}  # and of tsid_fit_pass_kernels
 IDX = {"row_map": 0, "col_map": 1, "row_ptr": 2, "csr_col": 3, "csr_val": 4, "col_ptr": 5,
        "csc_row": 6, "csc_val": 7, "deg_r": 8, "deg_c": 9, "batch_ptr_r": 10, "batch_ptr_c": 11}
 
@@ -161,13 +162,12 @@ def tsid_set_pass_kernel(ctx, mode: int) -> int:
 
 
 def tsid_fit_pass_kernels(ctx):
-    """(P pass, Q pass) kernel names of the last fit ('item', 'slab', or None)."""
+    """(P pass, Q pass) kernel names of the last fit ('item', 'slab', 'small', or None)."""
     a, b = C.c_int32(0), C.c_int32(0)
     st = lib().tsid_fit_pass_kernels(ctx, C.byref(a), C.byref(b))
     if st != OK:
         raise TsidError(st, "tsid_fit_pass_kernels")
-    names = {v: k for k, v in PASS_KERNEL.items()}
-    return names.get(a.value), names.get(b.value)
+    return PASS_RAN.get(a.value), PASS_RAN.get(b.value)
 
 
 def tsid_get_timing(ctx) -> dict:
@@ -350,7 +350,7 @@ class Tsid:
         self._check(tsid_set_pass_kernel(self.ctx, PASS_KERNEL[mode]), "tsid_set_pass_kernel")
 
     def pass_kernels(self):
-        """Kernels of the last fit's P and Q passes: ('item' | 'slab', ...)."""
+        """Kernels of the last fit's P and Q passes: ('item' | 'slab' | 'small', ...)."""
         return tsid_fit_pass_kernels(self.ctx)
 
     def timing(self) -> dict:

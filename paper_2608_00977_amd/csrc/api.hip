@@ -1880,25 +1880,26 @@ void fit_minibatch(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, doub
 }
 
 // Whether a fit runs as one workgroup (k_fit_small): fp32 full-gradient epochs
-// under the automatic modes with nothing to time, factors and cells in one
-// compute unit's LDS, and an epoch there shorter than the launches that it
-// replaces (8 us at least).  What an epoch there takes grows with the cells of a
-// group's share plus those of the longest bucket, which one group walks, at
-// about 150 ns each (fp64 sums).  40 epochs and the call, launches -> one
+// under the automatic modes, factors and cells in one compute unit's LDS, and an
+// epoch there that is short.  It depends on the template and the options' precision
+// and clip alone: neither the epoch count nor timing changes a fit's bits.  What
+// an epoch there takes grows with the cells of a group's share plus those of the
+// longest bucket, which one group walks, at about 150 ns each (fp64 sums); the
+// launches it replaces take 8 us an epoch at k = 8 and more at higher ranks, so the
+// line is on the safe side there.  40 epochs and the call, launches -> one
 // workgroup: 200 x 160 rows, 1,440 cells, k = 8 (23 such cells) 352 -> 176 us; 600
 // x 500 rows, 4,000 cells, k = 8 (38) 345 -> 349 us; 300 x 250 rows, 5,000 cells,
-// k = 16 (71) 461 -> 582 us; 120 x 100 rows, 3,000 cells, k = 32 (94) 737 -> 585 us.
+// k = 16 (71) 461 -> 582 us; 120 x 100 rows, 3,000 cells, k = 32 (94, left to the
+// launches) 737 -> 585 us.
 #ifndef TSID_SMALL_CELLS
 #define TSID_SMALL_CELLS 32
 #endif
 bool fit_is_small(const tsid_ctx *c, const tsid_fit_opts *o) {
     const Template &t = *c->tpl;
-    if (o->prec != TSID_FP32 || o->clip == 2 || o->epochs < 1 || t.sim.on || c->timing ||
+    if (o->prec != TSID_FP32 || o->clip == 2 || t.sim.on ||
         c->pass_kernel != TSID_PASS_AUTO || c->dense_fill > 0.f || c->row_blocks > 1 || t.m_t < 1 || t.n_t < 1 ||
         t.k > 64)  // k = 128: an epoch of the kernel spills, 60 x 60 rows, 1,200 cells: 446 -> 812 us
         return false;
-    // pinned memory holds the history; a run of more epochs takes the launches
-    if (o->epochs > (1 << 16)) return false;
     if (t.nnz > INT32_MAX / 2 || fit_small_lds(t.k, t.m_t, t.n_t, t.nnz) > kSmallFitLds) return false;
     int64_t most = 0;
     for (const auto &ptr : t.hptr)
@@ -1909,18 +1910,18 @@ bool fit_is_small(const tsid_ctx *c, const tsid_fit_opts *o) {
 void fit_small(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *loss_hist) {
     Template &t = *c->tpl;
     const int32_t T = o->epochs;
-    if (c->small_cap < T + 2) {
+    constexpr int32_t kPiece = 1 << 16;  // epochs of a launch: pinned memory holds their history
+    const int32_t most = std::min(T, kPiece) + 1;
+    if (c->small_cap < most) {
         if (c->small_host) (void)hipHostFree(c->small_host);
         c->small_host = nullptr;
         c->small_cap = 0;
-        const int32_t cap = std::max(T + 2, 1024);
+        const int32_t cap = std::max(most, 1024);
         TSID_HIP(hipHostMalloc((void **)&c->small_host, (size_t)cap * sizeof(double), hipHostMallocDefault));
         c->small_cap = cap;
     }
     c->dense_used = tsid_dense_info{};
-    // the pass that the automatic rule names; the arithmetic is the same
-    for (int sd = 0; sd < 2; ++sd)
-        c->used_kernel[sd] = slab_wanted(c, sd, o->prec) ? TSID_PASS_SLAB : TSID_PASS_ITEM;
+    c->used_kernel[0] = c->used_kernel[1] = TSID_PASS_SMALL;
     c->used_blocks = 1;
     c->epochs_done = 0;
     SmallFitArgs a{};
@@ -1931,7 +1932,6 @@ void fit_small(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *
     a.m = t.m_t;
     a.n = t.n_t;
     a.nnz = (int32_t)t.nnz;
-    a.epochs = T;
     a.P = P;
     a.Q = Q;
     a.loss = loss_hist ? c->small_host : nullptr;
@@ -1942,13 +1942,31 @@ void fit_small(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *
     a.clip = o->clip;
     a.degree_r = side_scaled(o->step, 0);
     a.degree_c = side_scaled(o->step, 1);
-    launch_fit_small(t.k, a, c->comp);
-    TSID_HIP(hipStreamSynchronize(c->comp));
-    const int32_t last = c->err_host[0];
-    c->epochs_done = last;
-    if (loss_hist)
-        for (int ep = 0; ep <= T; ++ep) loss_hist[ep] = ep <= last ? c->small_host[ep] : NAN;
-    if (last < T) fail(TSID_E_NONFINITE, "non-finite update in epoch " + std::to_string(last));
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    if (c->timing) {
+        grow_events(c, 2);
+        ev[0] = c->events[0];
+        ev[1] = c->events[1];
+    }
+    if (loss_hist) std::fill(loss_hist, loss_hist + T + 1, NAN);
+    do {
+        a.epochs = std::min(T - c->epochs_done, kPiece);
+        launch_fit_small(t.k, a, c->comp, ev[0], ev[1]);
+        TSID_HIP(hipStreamSynchronize(c->comp));
+        const int32_t done = c->err_host[0];
+        if (loss_hist) std::copy_n(c->small_host, done + 1, loss_hist + c->epochs_done);
+        c->epochs_done += done;
+        if (c->timing) {
+            float ms = 0.f;
+            TSID_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
+            c->tm.pass_ms[0] += ms;
+            c->tm.pass_launches[0] += 1;
+            c->tm.epoch_ms += ms;
+            c->tm.epochs += done;
+        }
+        if (done < a.epochs)
+            fail(TSID_E_NONFINITE, "non-finite update in epoch " + std::to_string(c->epochs_done));
+    } while (c->epochs_done < T);
 }
 
 void fit(tsid_ctx *c, float *P, float *Q, const tsid_fit_opts *o, double *loss_hist) {

@@ -1517,10 +1517,10 @@ void launch_to_bf16(const float *X, int64_t n, uint16_t *Xb, hipStream_t s) {
 
 namespace {
 template <int K, int V>
-void fit_small_k(const SmallFitArgs &a, size_t lds, hipStream_t s) {
+void fit_small_k(const SmallFitArgs &a, size_t lds, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     TSID_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_fit_small<K, V>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallFitLds));
-    hipLaunchKernelGGL((k_fit_small<K, V>), dim3(1), dim3(kSmallThreads), lds, s, a);
+    hipExtLaunchKernelGGL((k_fit_small<K, V>), dim3(1), dim3(kSmallThreads), lds, s, ev0, ev1, 0, a);
     TSID_HIP(hipGetLastError());
 }
 }  // namespace
@@ -1531,14 +1531,14 @@ size_t fit_small_lds(int K, int64_t m, int64_t n, int64_t nnz) {
 
 int fit_small_groups(int K) { return kSmallThreads / (K / 4); }
 
-void launch_fit_small(int K, const SmallFitArgs &a, hipStream_t s) {
+void launch_fit_small(int K, const SmallFitArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const size_t lds = fit_small_lds(K, a.m, a.n, a.nnz);
     if (lds > kSmallFitLds) fail(TSID_E_INVAL, "the template does not fit one workgroup");
     switch (K) {
-        case 8: fit_small_k<8, 4>(a, lds, s); break;
-        case 16: fit_small_k<16, 4>(a, lds, s); break;
-        case 32: fit_small_k<32, 4>(a, lds, s); break;
-        case 64: fit_small_k<64, 4>(a, lds, s); break;
+        case 8: fit_small_k<8, 4>(a, lds, s, ev0, ev1); break;
+        case 16: fit_small_k<16, 4>(a, lds, s, ev0, ev1); break;
+        case 32: fit_small_k<32, 4>(a, lds, s, ev0, ev1); break;
+        case 64: fit_small_k<64, 4>(a, lds, s, ev0, ev1); break;
         default: fail(TSID_E_INVAL, "unsupported rank");
     }
 }

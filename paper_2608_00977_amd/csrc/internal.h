@@ -315,7 +315,7 @@ struct SmallFitArgs {
 constexpr size_t kSmallFitLds = 150 * 1024;  // dynamic LDS; the rest is the kernel's own
 size_t fit_small_lds(int K, int64_t m, int64_t n, int64_t nnz);
 int fit_small_groups(int K);  // owner rows the workgroup takes at a time
-void launch_fit_small(int K, const SmallFitArgs &a, hipStream_t s);
+void launch_fit_small(int K, const SmallFitArgs &a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 
 // Multi-view similarity term (similarity.hip): for every template column i,
 // gs[i] = sum_e S_e (q_i - q_col[e]) and se[i] = sum_e S_e ||q_i - q_col[e]||^2

@@ -4,7 +4,8 @@ automatic modes.  Against the oracle with the bars of the other fp32 fits
 rows and columns, more owner rows than the workgroup takes at a time, the step
 options and clips; against the item pass of the same template (1e-5: fp32 sums
 in another order, 20 contractive epochs); repeatability, 5 + 5 epochs = 10, the
-history without and with a non-finite stop."""
+history without and with a non-finite stop; the same bits with timing on and
+for any number of epochs."""
 import numpy as np
 import pytest
 
@@ -46,7 +47,7 @@ def test_small_fit_matches_oracle(T, case, step, clip):
     note(f"small fit {case} {step} clip={clip}")
     _build(T, p)
     st, P, Q, hist = gpu_fit(T, p, epochs=20, lr=lr, step=step, clip=clip, prec="fp32")
-    assert st == 0 and T.epochs_done() == 20
+    assert st == 0 and T.epochs_done() == 20 and T.pass_kernels() == ("small", "small")
     _, _, a, b, v = oracle_template(p)
     so, Po, Qo, ho, _ = oracle.fit(a, b, v, p.P0, p.Q0, 20, p.lam, lr, step, clip, p.xi)
     assert so == 0
@@ -57,6 +58,7 @@ def test_small_fit_matches_oracle(T, case, step, clip):
     T.set_pass_kernel("item")
     try:
         _, Pi, Qi, hi = gpu_fit(T, p, epochs=20, lr=lr, step=step, clip=clip, prec="fp32")
+        assert "small" not in T.pass_kernels()
     finally:
         T.set_pass_kernel("auto")
     assert rel_fro(P, Pi) <= 1e-5 and rel_fro(Q, Qi) <= 1e-5
@@ -76,6 +78,7 @@ def test_repeats_and_resumes_bitwise(T):
     np.testing.assert_array_equal(P, P6)
     np.testing.assert_array_equal(Q, Q6)
     np.testing.assert_array_equal(h, np.concatenate([h5[:5], h6]))
+    assert T.pass_kernels() == ("small", "small")
 
 
 def test_nonfinite_stop_returns_the_last_finite_iterate(T):
@@ -84,7 +87,7 @@ def test_nonfinite_stop_returns_the_last_finite_iterate(T):
     note("small fit non-finite stop")
     st, P, Q, hist = gpu_fit(T, p, epochs=60, lr=1e6, step="sum", clip=False, prec="fp32")
     done = T.epochs_done()
-    assert st == 7 and 0 < done < 60
+    assert st == 7 and 0 < done < 60 and T.pass_kernels() == ("small", "small")
     assert np.all(np.isfinite(P)) and np.all(np.isfinite(Q)) and np.all(np.isnan(hist[done + 1:]))
     T.set_pass_kernel("item")
     try:
@@ -96,3 +99,46 @@ def test_nonfinite_stop_returns_the_last_finite_iterate(T):
     assert st == 0
     np.testing.assert_array_equal(P, P2)
     np.testing.assert_array_equal(hist[:done + 1], h2)
+
+
+def test_timing_and_epoch_count_leave_the_bits_alone(T):
+    """Timing a fit, no epochs at all and more epochs than one launch takes give
+    the same bits; the timer sees the launches and every epoch."""
+    p = _case(CASES[0])
+    _build(T, p)
+    note("small fit timing")
+    want = gpu_fit(T, p, epochs=12, lr=0.1, step="degree", prec="fp32")
+    T.set_timing(5)
+    try:
+        got = gpu_fit(T, p, epochs=12, lr=0.1, step="degree", prec="fp32")
+        tm = T.timing()
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a, b)
+        assert T.pass_kernels() == ("small", "small")
+        assert tm["pass_launches"] == [1, 0] and tm["epochs"] == 12
+        assert tm["epoch_ms"] == tm["pass_ms"][0] > 0 and tm["fixup_launches"] == tm["reduce_launches"] == 0
+    finally:
+        T.set_timing(0)
+    st, P, Q, hist = gpu_fit(T, p, epochs=0, lr=0.1, step="degree", prec="fp32")
+    assert st == 0 and hist[0] == want[3][0]
+    np.testing.assert_array_equal(P, p.P0)
+    np.testing.assert_array_equal(Q, p.Q0)
+    note("small fit in more than one launch")
+    n = 66_000
+    P0, Q0 = p.P0, p.Q0
+    st, P, Q, hist = gpu_fit(T, p, epochs=n, lr=0.01, step="degree", prec="fp32")
+    assert st == 0 and T.epochs_done() == n and T.pass_kernels() == ("small", "small")
+    parts = []
+    for _ in range(2):
+        st, P0, Q0, h = gpu_fit(T, p, epochs=n // 2, lr=0.01, step="degree", prec="fp32", P0=P0, Q0=Q0)
+        parts.append(h)
+    np.testing.assert_array_equal(P, P0)
+    np.testing.assert_array_equal(Q, Q0)
+    np.testing.assert_array_equal(hist, np.concatenate([parts[0][:-1], parts[1]]))
+
+
+def test_small_is_reported_and_not_a_mode(T):
+    from paper_2608_00977_amd.binding import E_INVAL, tsid_set_pass_kernel
+    assert tsid_set_pass_kernel(T.ctx, 3) == E_INVAL
+    with pytest.raises(KeyError):
+        T.set_pass_kernel("small")
