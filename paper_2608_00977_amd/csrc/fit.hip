@@ -1346,13 +1346,19 @@ void extend_steps_buf(const PassArgs &a, int32_t steps, int64_t nnz, const ExtLi
     hipLaunchKernelGGL((k_extend_steps<K, V, BUF>), dim3(ceil_div(a.rows, (int64_t)kWaves)), dim3(kThreads), 0, s, a,
                        steps);
     TSID_HIP(hipGetLastError());
-    if (nnz <= ext_capacity<K, V>(1)) return;
+    // the longest row that can be listed: the whole chunk, or one cell below the
+    // Gram form's threshold.  Forms it does not reach have no row: empty launches of
+    // 2 to 3 us each, five a chunk where that threshold is one wave's capacity or less
+    // (k = 32, 20 steps, a table in L2: rows from 40 cells, and one wave holds 128)
+    const int64_t longest = a.skip_from > 0 ? std::min(nnz, a.skip_from - 1) : nnz;
+    if (longest <= ext_capacity<K, V>(1)) return;
     hipLaunchKernelGGL((k_extend_lists<K, V>), dim3(ceil_div(a.rows, (int64_t)kThreads)), dim3(kThreads), 0, s, a, l);
     TSID_HIP(hipGetLastError());
     // at most nnz / (capacity + 1) rows are longer than a form's capacity
     auto group = [&](auto kernel, int w, int waves) {
-        const int64_t most = std::min<int64_t>(a.rows, nnz / (ext_capacity<K, V>(w ? kExtForms[w - 1] : 1) + 1));
-        if (most <= 0) return;
+        const int64_t below = ext_capacity<K, V>(w ? kExtForms[w - 1] : 1);
+        const int64_t most = std::min<int64_t>(a.rows, nnz / (below + 1));
+        if (longest <= below || most <= 0) return;
         // twice as many workgroups as fit at two waves per SIMD
         const int64_t grid = std::min<int64_t>(most, 2 * 256 * 8 / waves);
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), 0, s, a, steps, (const int32_t *)l.rows[w],

@@ -547,7 +547,11 @@ bool ridge_supported(int K) { return K == 8 || K == 16 || K == 32 || K == 64 || 
 // blocks it forms, the pairs I <= J) and, per step, the product G x with x
 // broadcast lane by lane (about 3 K wave instructions).  Per-cell form: 2 K
 // fp32 multiply-adds per cell and step, and the gathers of the row's fixed
-// rows again every step.
+// rows.  The line was measured when the per-cell form gathered them again every
+// step, as it does now beyond a workgroup's registers only; shorter rows
+// are often faster per cell by now (k = 64, 96 cells, a 128 MB table: 388 us a
+// chunk against 738), and keep the Gram form for its fp64 sums (error against 64
+// bits 4.7e-8 against 9.1e-8).
 //  - A fixed table within one XCD's L2 (4 MiB) serves those gathers from L2,
 //    and the forms compare by arithmetic: d = T K / (2 T - K r), when
 //    2 T > K r.  Rating-shaped rows (k = 64, 20 steps, a 2 MiB table): all in

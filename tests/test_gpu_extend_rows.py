@@ -5,7 +5,7 @@ against the oracle's one-sided steps of the same cells (1e-4 relative per row,
 the fp32 bar of the extension: 20 steps of sums of a few thousand terms, a
 few 1e-7 each).  The Gram form is off, so every row takes the per-cell form.
 A second run in chunks gives the same bits: a row's form depends on its own
-length alone."""
+length alone.  Forms that no row can take are not launched."""
 import numpy as np
 import pytest
 
@@ -68,3 +68,41 @@ def test_nonfinite_step_is_reported_from_every_form(T):
         with _gram_env(-1), pytest.raises(tsid.TsidError) as e:
             _run(T, F, fixed, free, r, 1, tsid.make_opts(epochs=30, lam=0.0, lr=1e30, step="sum"))
         assert e.value.status == 7
+
+
+def _kernels(run):
+    """Names of the kernels that run() launches, from the runtime's trace."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        run()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events()]
+
+
+@pytest.mark.parametrize("k", [8, 32, 64])
+def test_forms_without_a_row_are_not_launched(T, k):
+    """Rows at or above the Gram threshold leave the per-cell forms: the list
+    kernel and a workgroup form are launched only where the threshold (or the
+    chunk) leaves room for a row beyond the form before it, and the results do not
+    depend on that."""
+    from paper_2608_00977_amd import make_opts
+    caps = CAPS[k]
+    lengths = [caps[3] + 200, 30, caps[2], caps[3] + 3]
+    F, fixed, free, r = _chunk(5 + k, k, caps[3] + 500, lengths)
+    _set_rank(T, k)
+    opts = make_opts(epochs=20, lam=0.05, lr=0.05, step="degree")
+    st, Xo = oracle.extend(fixed, free, r, len(lengths), F, 20, 0.05, 0.05, "degree", False, 0.05)
+    assert st == 0
+    for threshold, forms in ((16, 0), (caps[0], 0), (caps[0] + 1, 0), (caps[0] + 2, 1), (caps[1] + 1, 1),
+                             (caps[1] + 2, 2), (caps[2] + 2, 3), (caps[3] + 1, 3), (caps[3] + 2, 4), (-1, 4)):
+        note(f"extend launches k={k} threshold {threshold}")
+        with _gram_env(threshold):
+            out = []
+            names = _kernels(lambda: out.append(_run(T, F, fixed, free, r, len(lengths), opts)))
+        if not any("k_extend_steps" in n for n in names):
+            pytest.skip("no kernel trace on this machine")
+        assert sum("k_extend_lists" in n for n in names) == (forms > 0)
+        assert sum("k_extend_group" in n for n in names) == forms
+        assert _row_err(out[0], Xo).max() <= 1e-4
