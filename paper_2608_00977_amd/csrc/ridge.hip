@@ -64,7 +64,11 @@ struct RidgeShape {
 // and its records load a round earlier, so a row alone on its SIMD (long
 // rows are few) does not wait for the two memory round trips, and a group's
 // conversions issue under the products of the one before.  Loads past the
-// row's end re-read its last cell and count as zero.
+// row's end re-read its last cell.  The last round stands apart: the full ones
+// need no masks (which keeps k = 32 at four waves a SIMD), and it takes only the
+// groups that have a cell, so a row of two cells loads and multiplies one group,
+// not U.  Chunks of 12 M cells in Gram form (k = 32, 20 steps), rows of 100 /
+// 1,000 cells: 1,337 / 752 -> 1,096 / 605 us with the last round apart.
 template <int K>
 __device__ __forceinline__ void gram_line(const RidgeArgs &A, int64_t b0, int64_t b1, int lane,
                                           d4 (&acc)[RidgeShape<K>::NP], double (&rhs)[RidgeShape<K>::NB]) {
@@ -92,33 +96,48 @@ __device__ __forceinline__ void gram_line(const RidgeArgs &A, int64_t b0, int64_
 #pragma unroll
         for (int I = 0; I < S::NB; ++I) raw[u][I] = p[(K % 16 == 0 || 16 * I + lr < K) ? 16 * I + lr : K - 1];
     };
+    auto products = [&](const double rv, const double (&pv)[S::NB]) {
+        int q = 0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_record(u, 0);
+        for (int I = 0; I < S::NB; ++I) {
+            rhs[I] = fma(rv, pv[I], rhs[I]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_row(u);
+            for (int J = I; J < S::NB; ++J, ++q)
+                acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[I], pv[J], acc[q], 0, 0, 0);
+        }
+    };
+    auto inside = [&](int I) { return K % 16 == 0 || 16 * I + lr < K; };
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_record(u, 4 * U);
-    for (int64_t c0 = b0; c0 < b1; c0 += 4 * U, first += 4 * U) {
-        left = left_from(c0);
+    for (int u = 0; u < U; ++u)
+        if (4 * u < left) load_record(u, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (4 * u < left) load_row(u);
+    if (left > 4 * U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_record(u, 4 * U);
+    }
+    for (int64_t c0 = b0; left > 4 * U; c0 += 4 * U, first += 4 * U, left = left_from(c0)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = 4 * u + lq < left;
-            const double rv = in ? (double)val[u] : 0.0;
+            const double rv = (double)val[u];
             double pv[S::NB];
 #pragma unroll
-            for (int I = 0; I < S::NB; ++I)
-                pv[I] = (in && (K % 16 == 0 || 16 * I + lr < K)) ? (double)raw[u][I] : 0.0;
+            for (int I = 0; I < S::NB; ++I) pv[I] = inside(I) ? (double)raw[u][I] : 0.0;
             load_row(u);
             load_record(u, 8 * U);
-            int q = 0;
-#pragma unroll
-            for (int I = 0; I < S::NB; ++I) {
-                rhs[I] = fma(rv, pv[I], rhs[I]);
-#pragma unroll
-                for (int J = I; J < S::NB; ++J, ++q)
-                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[I], pv[J], acc[q], 0, 0, 0);
-            }
+            products(rv, pv);
         }
+    }
+    // the last round: the groups that have a cell
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (4 * u >= left) break;
+        const bool in = 4 * u + lq < left;
+        double pv[S::NB];
+#pragma unroll
+        for (int I = 0; I < S::NB; ++I) pv[I] = in && inside(I) ? (double)raw[u][I] : 0.0;
+        products(in ? (double)val[u] : 0.0, pv);
     }
 }
 
@@ -199,7 +218,10 @@ __device__ __forceinline__ double pivot_rsqrt(double d, bool &bad) {
 // k = 64, rows of about 97 cells: 446 -> 199 us a chunk of 10,000 rows (the
 // earlier form kept a row of the trailing matrix per lane and broadcast each
 // column element by element with readlane: 64 dependent steps, half of the
-// lanes idle).
+// lanes idle).  Rows of a few cells at k = 8 are bound by the instructions around
+// the one block: 1 M rows of 2 cells 1,137 us (1,568 in the earlier form, 2,474
+// while all four groups of the padded block were factored and every row took a
+// whole round of the Gram matrix).
 template <int K>
 __global__ __launch_bounds__(256, 2) void k_ridge_rows(const RidgeArgs A) {
     using S = RidgeShape<K>;
@@ -223,13 +245,15 @@ __global__ __launch_bounds__(256, 2) void k_ridge_rows(const RidgeArgs A) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (lr == 4 * j + lq) acc[at(I, I)][j] += 16 * I + lr < K ? (double)A.lambda : 1.0;
+    // groups of four rows of block row I; at k = 8 the block's other half stays apart
+    constexpr auto groups = [](int I) constexpr { return K - 16 * I < 16 ? (K - 16 * I) / 4 : 4; };
     const int ma = lr & 3;  // the row of M in this lane's A operand; its column is lq
     double mv[NB][4], zv[NB][4];  // per group: M[ma][lq], and z of row 4 s + lq
     bool bad = false;
 #pragma unroll
     for (int I = 0; I < NB; ++I) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < groups(I); ++s) {
             const double g = acc[at(I, I)][s];
             auto el = [&](int a, int c) { return readlane_f64(g, 16 * a + 4 * s + c); };
             const double d00 = el(0, 0), d01 = el(0, 1), d02 = el(0, 2), d03 = el(0, 3);
@@ -261,7 +285,7 @@ __global__ __launch_bounds__(256, 2) void k_ridge_rows(const RidgeArgs A) {
             }
 #pragma unroll
             for (int J = I; J < NB; ++J) {
-                if (J == I && s == 3) continue;  // block row I is done
+                if (J == I && s == groups(I) - 1) continue;  // block row I is done
                 // A rows of this block row that are already U are zero: they stay as they are
                 const double n = J > I || lr >= 4 * (s + 1) ? -u[J] : 0.0;
 #pragma unroll
@@ -287,7 +311,7 @@ __global__ __launch_bounds__(256, 2) void k_ridge_rows(const RidgeArgs A) {
 #pragma unroll
     for (int I = NB - 1; I >= 0; --I) {
 #pragma unroll
-        for (int s = 3; s >= 0; --s) {
+        for (int s = groups(I) - 1; s >= 0; --s) {
             double t = 0.0;
 #pragma unroll
             for (int J = I; J < NB; ++J) t = fma(acc[at(I, J)][s], x[J], t);
