@@ -2383,8 +2383,12 @@ void ext_ensure(tsid_ctx *c, int64_t nnz, int32_t n_free, int32_t k) {
     }
     if (nnz <= x.cap_nnz && n_free <= x.cap_free && k == x.k) return;
     ext_sync_all(c);  // buffers may be in use by earlier chunks
-    const int64_t cn = std::max<int64_t>({nnz, x.cap_nnz + x.cap_nnz / 2, 1024});
-    const int32_t cf = (int32_t)std::min<int64_t>(std::max<int64_t>({(int64_t)n_free, (int64_t)x.cap_free + x.cap_free / 2, 64}), INT32_MAX - 1);
+    // a size that no longer fits grows by half at least; another rank alone keeps both
+    auto grown = [](int64_t need, int64_t cap, int64_t least) {
+        return need <= cap ? cap : std::max({need, cap + cap / 2, least});
+    };
+    const int64_t cn = grown(nnz, x.cap_nnz, 1024);
+    const int32_t cf = (int32_t)std::min<int64_t>(grown(n_free, x.cap_free, 64), INT32_MAX - 1);
     int32_t *err_keep = x.err;
     x.err = nullptr;
     free_ext_buffers(c);

@@ -106,3 +106,20 @@ def test_forms_without_a_row_are_not_launched(T, k):
         assert sum("k_extend_lists" in n for n in names) == (forms > 0)
         assert sum("k_extend_group" in n for n in names) == forms
         assert _row_err(out[0], Xo).max() <= 1e-4
+
+
+def test_rank_changes_do_not_grow_the_buffers():
+    """A context that goes back and forth between ranks keeps buffers of the
+    largest chunk's size: 60 changes fit a cap of 64 MiB."""
+    import paper_2608_00977_amd as tsid
+    T = tsid.Tsid(0, max_device_bytes=64 << 20)
+    try:
+        note("extend rank changes")
+        for turn in range(60):
+            k = (8, 32)[turn % 2]
+            F, fixed, free, r = _chunk(turn, k, 300, [5, 40, 0, 200])
+            _set_rank(T, k)
+            X = _run(T, F, fixed, free, r, 4, tsid.make_opts(epochs=2, lam=0.1, lr=0.05, step="degree"))
+            assert np.all(np.isfinite(X)) and not X[2].any()
+    finally:
+        T.close()
