@@ -824,8 +824,8 @@ struct WaveSum {
 #endif
 constexpr int kExtCells = TSID_EXT_CELLS;
 constexpr int kExtGroupCells = TSID_EXT_GROUP_CELLS;
-// waves of the workgroup forms; the last one holds no cells and takes rows of
-// any length
+// waves of the workgroup forms; the last one holds no cells: it takes rows of
+// any length, and the others' rows when there are few steps
 constexpr int kExtForms[kExtLists] = {2, 4, 8, 4};
 template <int K, int V>
 constexpr int64_t ext_capacity(int waves) { return (int64_t)waves * (64 / (K / V)) * (waves > 1 ? kExtGroupCells : kExtCells); }
@@ -836,8 +836,10 @@ constexpr int64_t ext_capacity(int waves) { return (int64_t)waves * (64 / (K / V
 #endif
 
 // All steps of one free row by WAVES waves (WAVES = 1: this wave alone).
-// red: LDS of 2 x WAVES x 64 x N floats (WAVES > 1).
-template <int K, int V, bool BUF, int WAVES, bool STREAM>
+// red: LDS of 2 x WAVES x 64 x N floats (WAVES > 1).  ALONE (with STREAM): this
+// wave takes the shares of all WAVES waves in turn and adds their sums in the
+// same order, so the bits are those of the workgroup.
+template <int K, int V, bool BUF, int WAVES, bool STREAM, bool ALONE = false>
 __device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row, const int64_t rb, const int64_t deg,
                                            const int32_t steps, float *red) {
     constexpr int G = K / V;
@@ -848,12 +850,13 @@ __device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row,
     constexpr int SPLR = (CH + G - 1) / G;
     using W = WaveSum<G, V>;
     const int lane = threadIdx.x & 63;
-    const int wv = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
+    const int wv = WAVES > 1 && !ALONE ? (int)(threadIdx.x >> 6) : 0;
     const int grp = wv * NG + lane / G, lg = lane % G;
     const bool up8 = (lane & 8) != 0;
     constexpr int64_t groups = (int64_t)WAVES * NG;
     const int64_t beg = rb + grp * deg / groups, end = rb + (grp + 1) * deg / groups;
     const int64_t last = end - 1;
+    static_assert(STREAM || !ALONE, "a wave alone holds no other wave's cells");
     const float s = A.degree ? 1.0f / (float)(deg > 1 ? deg : 1) : 1.0f;
     const YTable Yt = make_ytable<BUF>(A, K * 4);
     float x[V], xo[W::N];
@@ -861,8 +864,16 @@ __device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row,
     for (int v = 0; v < V; ++v) x[v] = 0.f;
 #pragma unroll
     for (int i = 0; i < W::N; ++i) xo[i] = 0.f;
-    // The gradient sum over the groups (and the waves, in wave order), the
-    // update of the coordinates this lane owns, and the row back to all lanes.
+    // The update of the coordinates this lane owns, and the row back to all lanes.
+    auto move = [&](const float (&own)[W::N]) {
+#pragma unroll
+        for (int i = 0; i < W::N; ++i) {
+            const float g = 2.0f * A.lam * xo[i] - 2.0f * own[i];
+            xo[i] += A.lr * clipped_step(g, s, A.clip, A.xi);
+        }
+        W::spread(xo, x, up8);
+    };
+    // The gradient sum over the groups (and the waves, in wave order), then move.
     auto update = [&](const float (&acc)[V], const int st) {
         float own[W::N];
         W::sum(acc, own, up8);
@@ -879,12 +890,7 @@ __device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row,
                 for (int w = 1; w < WAVES; ++w) own[i] += buf[(w * W::N + i) * 64 + lane];
             }
         }
-#pragma unroll
-        for (int i = 0; i < W::N; ++i) {
-            const float g = 2.0f * A.lam * xo[i] - 2.0f * own[i];
-            xo[i] += A.lr * clipped_step(g, s, A.clip, A.xi);
-        }
-        W::spread(xo, x, up8);
+        move(own);
     };
     if constexpr (!STREAM) {
         // the largest share of a group, the same for every lane
@@ -956,32 +962,58 @@ __device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row,
             update(acc, st);
         }
     } else {
-        // longer than a compute unit's registers hold: the groups walk their
-        // shares through the item pass's blocks again every step
+        // longer than a compute unit's registers hold, or few steps: the groups walk
+        // their shares through the item pass's blocks again every step
         constexpr int SPL = 4 * G % chunk_cells<G>() == 0 ? 4 : chunk_cells<G>() / G;
         constexpr int SB = G * SPL;
         const uint32_t xp[V / 2] = {};  // bf16 pairs: unused in fp32
         int2 bufA[SPL], bufB[SPL];
-        for (int st = 0; st < steps; ++st) {
-            float acc[V];
+        // Wave w's cells are whole rounds of the wave (a chunk for each of its
+        // groups) as far as the row goes, so that only the row's last round is
+        // padded; a group's cells are neighbours.
+        constexpr int64_t C = chunk_cells<G>(), ROUND = NG * C;
+        const int64_t rounds = (deg + ROUND - 1) / ROUND;
+        auto walk = [&](const int w, float (&acc)[V]) {
+            const int64_t r0 = w * rounds / WAVES, r1 = (w + 1) * rounds / WAVES, per = (r1 - r0) * C;
+            const int64_t e = rb + (r1 * ROUND < deg ? r1 * ROUND : deg);
+            const int64_t b = rb + r0 * ROUND + lane / G * per;
+            const int64_t sb = b < e ? b : e, se = sb + per < e ? sb + per : e, sl = se - 1;
+            float e2 = 0.f;
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] = 0.f;
-            float e2 = 0.f;
-            if (end > beg) {
+            if (se > sb) {
 #pragma unroll
                 for (int c = 0; c < SPL; ++c) {
-                    const int64_t jj = beg + c * G + lg;
-                    bufA[c] = load_cell(A.stream + (jj < last ? jj : last));
+                    const int64_t jj = sb + c * G + lg;
+                    bufA[c] = load_cell(A.stream + (jj < sl ? jj : sl));
                 }
             }
-            for (int64_t j0 = beg; j0 < end; j0 += SB) {
-                process_block<K, V, false, false, BUF, true, SPL>(A, Yt, j0, end, last, lg, bufA, bufB, x, xp, acc,
-                                                                  e2);
+            for (int64_t j0 = sb; j0 < se; j0 += SB) {
+                process_block<K, V, false, false, BUF, true, SPL>(A, Yt, j0, se, sl, lg, bufA, bufB, x, xp, acc, e2);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int c = 0; c < SPL; ++c) bufA[c] = bufB[c];
             }
-            update(acc, st);
+        };
+        for (int st = 0; st < steps; ++st) {
+            float acc[V];
+            if constexpr (ALONE) {
+                float tot[W::N];
+#pragma unroll
+                for (int i = 0; i < W::N; ++i) tot[i] = 0.f;
+#pragma unroll 1
+                for (int w = 0; w < WAVES; ++w) {
+                    walk(w, acc);
+                    float own[W::N];
+                    W::sum(acc, own, up8);
+#pragma unroll
+                    for (int i = 0; i < W::N; ++i) tot[i] = w == 0 ? own[i] : tot[i] + own[i];
+                }
+                move(tot);
+            } else {
+                walk(wv, acc);
+                update(acc, st);
+            }
         }
     }
     if (grp == 0) store_coords<G, V, false>(A.Xn + row * K, lg, x);
@@ -996,9 +1028,10 @@ __device__ __forceinline__ void extend_row(const PassArgs &A, const int64_t row,
 // The rows longer than one wave's capacity, listed by the workgroup form that
 // takes them (the lists' order is of no account: rows are independent).  One
 // thread per row and one atomic add per list and workgroup: adds to one
-// address from every row's wave took 15 ns each.
+// address from every row's wave took 15 ns each.  stream: the forms (bits) whose
+// rows go to the last one.
 template <int K, int V>
-__global__ __launch_bounds__(kThreads) void k_extend_lists(const PassArgs A, const ExtLists L) {
+__global__ __launch_bounds__(kThreads) void k_extend_lists(const PassArgs A, const ExtLists L, const uint32_t stream) {
     __shared__ uint32_t n[kExtLists], base[kExtLists];
     if (threadIdx.x < kExtLists) n[threadIdx.x] = 0;
     __syncthreads();
@@ -1010,6 +1043,7 @@ __global__ __launch_bounds__(kThreads) void k_extend_lists(const PassArgs A, con
         if (deg > ext_capacity<K, V>(1) && !(A.skip_from > 0 && deg >= A.skip_from)) {
             w = 0;
             while (w < kExtLists - 1 && deg > ext_capacity<K, V>(kExtForms[w])) ++w;
+            if (stream >> w & 1) w = kExtLists - 1;
             at = atomicAdd(&n[w], 1u);
         }
     }
@@ -1034,25 +1068,39 @@ __global__ __launch_bounds__(kThreads, K >= 64 ? 3 : 4) void k_extend_steps(cons
 
 // The listed rows, one workgroup of WAVES waves each, dealt in turn (the lists
 // come in about row order, so neighbours in length); the next row's place is
-// read while this one's steps run.
+// read while this one's steps run.  STREAM, with at least `alone` rows listed:
+// those of at most alone_cells cells go to one wave each, after the longer ones.
 template <int K, int V, bool BUF, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) void k_extend_group(const PassArgs A, int32_t steps, const int32_t *list,
-                                                             const uint32_t *count) {
+                                                             const uint32_t *count, uint32_t alone,
+                                                             int64_t alone_cells) {
     __shared__ float red[2 * WAVES * 64 * WaveSum<K / V, V>::N];
     const uint32_t n = *count;
+    const int64_t by_wave = STREAM && n >= alone ? alone_cells : -1;
     uint32_t q = blockIdx.x;
-    if (q >= n) return;
-    int64_t row = list[q], rb = A.ptr[row], re = A.ptr[row + 1];
-    for (;;) {
-        q += gridDim.x;
-        const int64_t nrow = q < n ? list[q] : row;
-        const int64_t nrb = A.ptr[nrow], nre = A.ptr[nrow + 1];
-        __syncthreads();  // the previous row's last reads of red are done
-        extend_row<K, V, BUF, WAVES, STREAM>(A, row, rb, re - rb, steps, red);
-        if (q >= n) return;  // the same for the whole workgroup
-        row = nrow;
-        rb = nrb;
-        re = nre;
+    if (q < n) {
+        int64_t row = list[q], rb = A.ptr[row], re = A.ptr[row + 1];
+        for (;;) {  // the same turns for the whole workgroup
+            q += gridDim.x;
+            const int64_t nrow = q < n ? list[q] : row;
+            const int64_t nrb = A.ptr[nrow], nre = A.ptr[nrow + 1];
+            if (!STREAM || re - rb > by_wave) {
+                __syncthreads();  // the previous row's last reads of red are done
+                extend_row<K, V, BUF, WAVES, STREAM>(A, row, rb, re - rb, steps, red);
+            }
+            if (q >= n) break;
+            row = nrow;
+            rb = nrb;
+            re = nre;
+        }
+    }
+    if constexpr (STREAM) {
+        if (by_wave < 0) return;
+        const uint32_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        for (uint32_t p = blockIdx.x * WAVES + wv; p < n; p += gridDim.x * WAVES) {
+            const int64_t row = list[p], rb = A.ptr[row], deg = A.ptr[row + 1] - rb;
+            if (deg <= by_wave) extend_row<K, V, BUF, WAVES, true, true>(A, row, rb, deg, steps, nullptr);
+        }
     }
 }
 
@@ -1352,23 +1400,57 @@ void extend_steps_buf(const PassArgs &a, int32_t steps, int64_t nnz, const ExtLi
     // (k = 32, 20 steps, a table in L2: rows from 40 cells, and one wave holds 128)
     const int64_t longest = a.skip_from > 0 ? std::min(nnz, a.skip_from - 1) : nnz;
     if (longest <= ext_capacity<K, V>(1)) return;
-    hipLaunchKernelGGL((k_extend_lists<K, V>), dim3(ceil_div(a.rows, (int64_t)kThreads)), dim3(kThreads), 0, s, a, l);
+    // With few steps a row's one gather into registers is not spread over enough of
+    // them: the forms hold two waves a SIMD, and a form that is half empty (rows just
+    // beyond the one before it) fewer cells still, where the streaming form keeps
+    // more waves and loads in flight.  From the first step on when the table lies
+    // beyond L2 (each further step gathers from there again), for a few steps when it
+    // lies in L2.  12 M cells, registers -> streaming, us: k = 128, 100 cells, table in L2,
+    // 1 / 2 steps 1,021 -> 602 / 1,185 -> 936, beyond L2 1,414 -> 1,075 / 1,546 ->
+    // 1,856; k = 32, 780 cells, in L2, 5 / 10 steps 691 -> 542 / 1,032 -> 895; k = 64,
+    // 780 cells, in L2, 3 / 4 steps 731 -> 583 / 819 -> 709.
+    const bool in_l2 = a.y_rows * (int64_t)K * 4 <= (int64_t(4) << 20);
+    constexpr int32_t kFew[3] = {K == 128 ? 2 : K == 32 ? 3 : 1, K == 128 ? 3 : K == 64 ? 2 : K == 32 ? 5 : 1,
+                                 K == 128 ? 7 : K == 64 ? 4 : K == 32 ? 10 : 1};
+    uint32_t stream = 0;
+    for (int w = 0; w < kExtLists - 1; ++w)
+        if (steps <= (in_l2 ? kFew[w] : 1)) stream |= 1u << w;
+    hipLaunchKernelGGL((k_extend_lists<K, V>), dim3(ceil_div(a.rows, (int64_t)kThreads)), dim3(kThreads), 0, s, a, l,
+                       stream);
     TSID_HIP(hipGetLastError());
+    // Streaming rows go to one wave each, with the same bits, where they are many:
+    // four waves a row pay a barrier a step and drain four times as often, and are
+    // worth it while the chip is not full.  Beyond L2, where a wave mostly waits,
+    // that is soon so; in L2 a last wave that is nearly empty costs more until the rows
+    // are three times the 2,048 waves that fit at k = 128.  A row of more than a
+    // 1,024th of the chunk keeps its workgroup, or it would run on alone.  k = 128, 20
+    // steps, four waves -> one: 12,000 rows of 1,000 cells, in L2, 5,243 -> 5,116 us; 2,222
+    // of 900, in L2, 910 -> 1,095; beyond L2 1,200 of 10,000, 15,400 -> 9,612, and
+    // 1,250 of 1,600, 2,705 -> 2,436.
+    const uint32_t alone = in_l2 ? 6144 : 1024;
     // at most nnz / (capacity + 1) rows are longer than a form's capacity
     auto group = [&](auto kernel, int w, int waves) {
-        const int64_t below = ext_capacity<K, V>(w ? kExtForms[w - 1] : 1);
+        if (stream >> w & 1) return;
+        int lowest = w;
+        if (w == kExtLists - 1 && stream) lowest = __builtin_ctz(stream);
+        const int64_t below = ext_capacity<K, V>(lowest ? kExtForms[lowest - 1] : 1);
         const int64_t most = std::min<int64_t>(a.rows, nnz / (below + 1));
         if (longest <= below || most <= 0) return;
         // twice as many workgroups as fit at two waves per SIMD
         const int64_t grid = std::min<int64_t>(most, 2 * 256 * 8 / waves);
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), 0, s, a, steps, (const int32_t *)l.rows[w],
-                           (const uint32_t *)(l.count + w));
+                           (const uint32_t *)(l.count + w), alone, nnz / 1024);
         TSID_HIP(hipGetLastError());
     };
     group(k_extend_group<K, V, BUF, kExtForms[0], false>, 0, kExtForms[0]);
     group(k_extend_group<K, V, BUF, kExtForms[1], false>, 1, kExtForms[1]);
     group(k_extend_group<K, V, BUF, kExtForms[2], false>, 2, kExtForms[2]);
-    group(k_extend_group<K, V, BUF, kExtForms[3], true>, 3, kExtForms[3]);
+    // streamed rows of k = 64 from beyond L2: 16 lanes a cell read its whole row with one
+    // load (1,200 rows of 10,000 cells, 5 steps 1,810 -> 1,446 us), in L2 8 lanes and fewer
+    // instructions are faster (4,000 rows of 2,000 cells, 20 steps 2,040 -> 1,814 us)
+    constexpr int SV = K == 64 ? 4 : V;
+    if (in_l2) group(k_extend_group<K, V, BUF, kExtForms[3], true>, 3, kExtForms[3]);
+    else group(k_extend_group<K, SV, BUF, kExtForms[3], true>, 3, kExtForms[3]);
 }
 
 template <int K, int V>

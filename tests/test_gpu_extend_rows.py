@@ -5,7 +5,8 @@ against the oracle's one-sided steps of the same cells (1e-4 relative per row,
 the fp32 bar of the extension: 20 steps of sums of a few thousand terms, a
 few 1e-7 each).  The Gram form is off, so every row takes the per-cell form.
 A second run in chunks gives the same bits: a row's form depends on its own
-length alone.  Forms that no row can take are not launched."""
+length alone.  Forms that no row can take are not launched.  With few steps longer
+rows are streamed, by one wave each where they are many, with the same bits."""
 import numpy as np
 import pytest
 
@@ -55,6 +56,62 @@ def test_rows_at_capacity_edges_match_oracle(T, k, step, clip):
             sel = (free >= lo) & (free < hi)
             parts.append(_run(T, F, fixed[sel], free[sel] - lo, r[sel], hi - lo, opts))
         np.testing.assert_array_equal(X, np.concatenate(parts))
+
+
+@pytest.mark.parametrize("k", [8, 16, 32, 64, 128])
+@pytest.mark.parametrize("steps", [0, 1, 2, 3, 5, 7, 8])
+def test_few_steps_match_oracle(T, k, steps):
+    """With few steps rows beyond one wave are streamed, up to a step count that
+    depends on the rank, the form and whether the table (the same rows, or more
+    that no cell names) lies within 4 MiB."""
+    from paper_2608_00977_amd import make_opts
+    caps = CAPS[k]
+    lengths = [0, 1, caps[0], caps[0] + 1, caps[0] + 40, caps[1], caps[1] + 1, caps[2] + 1, caps[3], caps[3] + 130]
+    F, fixed, free, r = _chunk(9 + k, k, caps[3] + 500, lengths)
+    _set_rank(T, k)
+    opts = make_opts(epochs=steps, lam=0.05, lr=0.05, step="degree", clip=True, xi=0.05)
+    st, Xo = oracle.extend(fixed, free, r, len(lengths), F, steps, 0.05, 0.05, "degree", True, 0.05)
+    assert st == 0
+    beyond = np.concatenate([F, np.zeros(((4 << 20) // (4 * k) + 1, k), np.float32)])
+    for table in (F, beyond):
+        note(f"extend rows, few steps k={k} steps={steps} table rows={table.shape[0]}")
+        with _gram_env(-1):
+            X = _run(T, table, fixed, free, r, len(lengths), opts)
+        err = _row_err(X, Xo)
+        assert err.max() <= 1e-4, (err.max(), lengths[int(err.argmax())])
+
+
+@pytest.mark.parametrize("k", [8, 32, 64, 128])
+@pytest.mark.parametrize("rows,in_l2", [(1700, False), (6300, True)])
+def test_many_streamed_rows_have_the_bits_of_few(T, k, rows, in_l2):
+    """Beyond a row count (1,024, or 6,144 with the table within 4 MiB) each streamed
+    row goes to one wave, except those of more than a 1,024th of the chunk: the same
+    bits as chunks of few rows, where a workgroup takes every one of them."""
+    from paper_2608_00977_amd import make_opts
+    g = np.random.default_rng(k)
+    lengths = CAPS[k][0] + 1 + g.integers(0, 70, rows)
+    lengths[[3, 900]] = CAPS[k][0] * 8 * (rows // 1000)
+    n_fixed = lengths.max() + 100
+    F = (g.standard_normal((n_fixed, k)) * k ** -0.5).astype(np.float32)
+    fixed = np.concatenate([np.sort(g.choice(n_fixed, n, replace=False)) for n in lengths]).astype(np.int32)
+    free = np.repeat(np.arange(lengths.size), lengths).astype(np.int32)
+    r = g.standard_normal(fixed.size).astype(np.float32)
+    assert lengths.max() > fixed.size // 1024 > np.sort(lengths)[-3]
+    assert F.nbytes <= 4 << 20
+    table = F if in_l2 else np.concatenate([F, np.zeros(((4 << 20) // (4 * k) + 1, k), np.float32)])
+    _set_rank(T, k)
+    opts = make_opts(epochs=1, lam=0.05, lr=0.05, step="degree")
+    note(f"many streamed rows k={k} rows={rows} cells={fixed.size}")
+    with _gram_env(-1):
+        X = _run(T, table, fixed, free, r, lengths.size, opts)
+        at = np.concatenate([[0], np.cumsum(lengths)])
+        for lo in range(0, lengths.size, 900):
+            hi = min(lengths.size, lo + 900)
+            s = slice(at[lo], at[hi])
+            part = _run(T, table, fixed[s], free[s] - lo, r[s], hi - lo, opts)
+            np.testing.assert_array_equal(X[lo:hi], part)
+    st, Xo = oracle.extend(fixed, free, r, lengths.size, F, 1, 0.05, 0.05, "degree", False, 0.05)
+    assert st == 0 and _row_err(X, Xo).max() <= 1e-4
 
 
 def test_nonfinite_step_is_reported_from_every_form(T):
