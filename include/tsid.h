@@ -195,7 +195,8 @@ tsid_status tsid_loss_noalloc(tsid_ctx *ctx, const float *P, const float *Q, flo
  * opts->prec is ignored: the fixed side is read in fp32).  A row's steps are
  * taken in one of two forms with the same result up to rounding:
  *  - per cell, in fp32, the row's fixed factors gathered once into registers
- *    (rows beyond a workgroup's registers gather them once per step);
+ *    (rows beyond a workgroup's registers, and with few steps all rows beyond
+ *    one wave's, gather them once per step);
  *  - in Gram form, for rows of at least a threshold number of cells: the
  *    gradient 2 lambda x - 2 (b - G x) from G = sum p p^T and b = sum r p,
  *    accumulated once in fp64 on the matrix cores, with the steps in fp64.
@@ -204,8 +205,9 @@ tsid_status tsid_loss_noalloc(tsid_ctx *ctx, const float *P, const float *Q, flo
  *    gathers are cheap): at 20 steps, from 40 (k = 32) or never (k = 64)
  *    cells with such a table, and from 69 (k = 32) or 96 (k = 64) cells
  *    with a larger one.  k = 128 and a single step keep the per-cell form.
- *    A row's form depends on its own cell count only, so results do not
- *    depend on how the rows are split into chunks.
+ *    A row's form depends on its own cell count, the rank, the step count
+ *    and the fixed table's size only, so results do not depend on how the
+ *    rows are split into chunks.
  * The chunk's cells are bucketed by free row on the device (a stable sort by
  * (free_local, fixed_id)); cells that already come in that order (as a
  * line-by-line generator emits them) skip the sort, with the same result.

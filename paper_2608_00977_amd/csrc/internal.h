@@ -273,8 +273,9 @@ void launch_block_combine(int K, int prec, const PassArgs &a, const float *part,
                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // `steps` one-sided extension steps from zero (a.rows buckets over a.stream /
 // a.ptr, nnz cells; fp32; a.X unused, the result goes to a.Xn; a non-finite
-// update stores 1 in a.err[ERR_NONFINITE]): one wave per short bucket, then one
-// workgroup per longer bucket, from the lists that the first launch leaves.
+// update stores 1 in a.err[ERR_NONFINITE]): one wave per short bucket, then
+// the longer ones from the lists that the second launch makes, a workgroup each,
+// or a wave each where those that are streamed are many.
 constexpr int kExtLists = 4;
 struct ExtLists {
     int32_t *rows[kExtLists];  // each a.rows long: the buckets of each workgroup form
